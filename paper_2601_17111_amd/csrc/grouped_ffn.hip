@@ -7,8 +7,8 @@
 //   out = act Wd_e                      GEMM 2
 //
 // This file: the tile list, the forward launcher, the float32 forward (one
-// thread per output element, reference precision, no matrix cores) and the
-// weight packing. The GEMM kernel itself is in gemm.h.
+// thread per output element, reference precision, no matrix cores). The GEMM
+// kernel itself is in gemm.h, the weight packing in pack.hip.
 #include <algorithm>
 #include <mutex>
 
@@ -608,57 +608,6 @@ hipError_t ffn_scratch_address(void **ptr) {
   }
   *ptr = addr[dev];
   return hipSuccess;
-}
-
-// ---------------------------------------------------------------------------
-// weight packing: tiled transposes (setup, not on the timed path)
-// ---------------------------------------------------------------------------
-
-// dst[b] at packed_index(map(c), r) = src[b][r][c]; map: 0 identity, 1 gate
-// slot, 2 up slot of the interleaved gate/up layout; the contraction index r
-// runs over the `rows` of src.
-template <typename T>
-__global__ __launch_bounds__(256) void transpose_kernel(const T *__restrict__ src, T *__restrict__ dst,
-                                                        int32_t rows, int32_t cols, int64_t sbs,
-                                                        int64_t dbs, int32_t mode) {
-  __shared__ T tile[64][65];
-  const int b = blockIdx.z, r0 = blockIdx.y * 64, c0 = blockIdx.x * 64;
-  const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-  for (int i = ty; i < 64; i += 4) {
-    const int r = r0 + i, c = c0 + tx;
-    if (r < rows && c < cols) tile[i][tx] = src[b * sbs + int64_t(r) * cols + c];
-  }
-  __syncthreads();
-  for (int i = ty; i < 64; i += 4) {
-    const int c = c0 + i, r = r0 + tx;
-    if (c < cols && r < rows) {
-      const int drow = mode == 0 ? c : 64 * (c / 32) + (c % 32) + (mode == 2 ? 32 : 0);
-      dst[b * dbs + packed_index(drow, r, rows)] = tile[tx][i];
-    }
-  }
-}
-
-template <typename T>
-static hipError_t pack_typed(int32_t E, int32_t D, int32_t F, const void *wg, const void *wu,
-                             const void *wd, void *gu, void *dn, hipStream_t stream) {
-  const dim3 blk(256);
-  const dim3 g_gu((F + 63) / 64, (D + 63) / 64, E);
-  const int64_t sbs = int64_t(D) * F, dbs_gu = int64_t(2) * F * D;
-  hipLaunchKernelGGL(transpose_kernel<T>, g_gu, blk, 0, stream, static_cast<const T *>(wg),
-                     static_cast<T *>(gu), D, F, sbs, dbs_gu, 1);
-  hipLaunchKernelGGL(transpose_kernel<T>, g_gu, blk, 0, stream, static_cast<const T *>(wu),
-                     static_cast<T *>(gu), D, F, sbs, dbs_gu, 2);
-  const dim3 g_dn((D + 63) / 64, (F + 63) / 64, E);
-  hipLaunchKernelGGL(transpose_kernel<T>, g_dn, blk, 0, stream, static_cast<const T *>(wd),
-                     static_cast<T *>(dn), F, D, sbs, sbs, 0);
-  return hipGetLastError();
-}
-
-hipError_t launch_pack(int32_t E, int32_t D, int32_t F, llep_dtype dtype, const void *w_gate,
-                       const void *w_up, const void *w_down, void *gu, void *dn,
-                       hipStream_t stream) {
-  if (dtype == LLEP_BF16) return pack_typed<uint16_t>(E, D, F, w_gate, w_up, w_down, gu, dn, stream);
-  return pack_typed<float>(E, D, F, w_gate, w_up, w_down, gu, dn, stream);
 }
 
 }  // namespace llep

@@ -273,46 +273,6 @@ void dact_kernel(GemmArgs g, WgradCopy w) {
   wgrad_copy_items(w, reinterpret_cast<uint16_t *>(smem + (threadIdx.x >> 6) * kCopyTileBytes));
 }
 
-// Packed weights for the backward GEMMs, in the forward's block layout:
-// [Wg | Wu] rows d with the gate/up columns interleaved per 32 (K = 2F), and
-// Wd rows f (K = D).
-template <typename T>
-__global__ __launch_bounds__(256) void pack_bwd_kernel(const T *__restrict__ wg,
-                                                       const T *__restrict__ wu,
-                                                       const T *__restrict__ wd, T *__restrict__ gut,
-                                                       T *__restrict__ dnt, int32_t E, int32_t D,
-                                                       int32_t F) {
-  const int64_t per = int64_t(D) * F, total = int64_t(E) * per;
-  for (int64_t u = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; u < total;
-       u += int64_t(gridDim.x) * blockDim.x) {
-    const int64_t e = u / per, r = u % per;
-    // Wg, Wu [E][D][F]: element (d, f)
-    const int d = int(r / F), f = int(r % F);
-    const int j = 64 * (f / 32) + (f % 32);
-    gut[e * 2 * per + packed_index(d, j, 2 * F)] = wg[u];
-    gut[e * 2 * per + packed_index(d, j + 32, 2 * F)] = wu[u];
-    // Wd [E][F][D]: element (f2, d2) = row f2 of the (K = D) packing
-    const int f2 = int(r / D), d2 = int(r % D);
-    dnt[e * per + packed_index(f2, d2, D)] = wd[u];
-  }
-}
-
-hipError_t launch_pack_backward(int32_t E, int32_t D, int32_t F, llep_dtype dtype, const void *w_gate,
-                                const void *w_up, const void *w_down, void *gut, void *dnt,
-                                hipStream_t stream) {
-  if (dtype == LLEP_F32)
-    hipLaunchKernelGGL(pack_bwd_kernel<float>, dim3(4096), dim3(256), 0, stream,
-                       static_cast<const float *>(w_gate), static_cast<const float *>(w_up),
-                       static_cast<const float *>(w_down), static_cast<float *>(gut),
-                       static_cast<float *>(dnt), E, D, F);
-  else
-    hipLaunchKernelGGL(pack_bwd_kernel<uint16_t>, dim3(4096), dim3(256), 0, stream,
-                       static_cast<const uint16_t *>(w_gate), static_cast<const uint16_t *>(w_up),
-                       static_cast<const uint16_t *>(w_down), static_cast<uint16_t *>(gut),
-                       static_cast<uint16_t *>(dnt), E, D, F);
-  return hipGetLastError();
-}
-
 // ---------------------------------------------------------------------------
 // float32 backward: one thread per output element (small layers; reference
 // precision, no matrix cores). Same operations and the same gradient-return
