@@ -350,6 +350,18 @@ int llep_grouped_ffn_backward(const llep_plan_params *params,
                               float *dw_up, float *dw_down, void *workspace,
                               size_t workspace_bytes, hipStream_t stream);
 
+/* Zeros for the weight gradients of the experts without a group in the range
+ * of `device` (or of all devices when device == -1): the experts that
+ * llep_grouped_ffn_backward on the same plan and device does not write, so
+ * that the two calls together write every element of dw_gate, dw_up and
+ * dw_down (in either order). Requirements on D, F and dw_* as there.
+ * Errors: LLEP_E_ARG. */
+int llep_zero_absent_gradients(const llep_plan_params *params,
+                               const llep_plan_buffers *plan, int32_t device,
+                               int32_t D, int32_t F, float *dw_gate,
+                               float *dw_up, float *dw_down,
+                               hipStream_t stream);
+
 /* Text of the calling thread's last error ("" if none). */
 const char *llep_last_error(void);
 

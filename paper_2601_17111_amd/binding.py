@@ -37,6 +37,7 @@ EXPORTED = [
     "llep_packed_down_bytes", "llep_last_error", "llep_combine_backward",
     "llep_pack_weights_backward", "llep_grouped_ffn_backward_workspace_bytes",
     "llep_grouped_ffn_backward", "llep_grouped_ffn_train", "llep_grouped_ffn_noalloc",
+    "llep_zero_absent_gradients",
 ]
 LLEP_NOALLOC_SCRATCH_BYTES = 64 << 20
 
@@ -109,6 +110,7 @@ def lib() -> ctypes.CDLL:
             "llep_grouped_ffn_backward": (ctypes.c_int, [pp, pb, i32, _P, _P, _P, _P, _P, _P,
                                                          i32, i32, ctypes.c_int, _P, _P, _P, _P,
                                                          _P, sz, _P]),
+            "llep_zero_absent_gradients": (ctypes.c_int, [pp, pb, i32, i32, i32, _P, _P, _P, _P]),
             "llep_last_error": (ctypes.c_char_p, []),
         }
         for name, (res, args) in sigs.items():
@@ -324,3 +326,12 @@ def llep_grouped_ffn_backward(params: llep_plan_params, bufs: PlanBuffers, devic
         _ptr(dx_perm), _ptr(dw_gate), _ptr(dw_up), _ptr(dw_down), _ptr(workspace),
         workspace.numel() * workspace.element_size(), _stream(stream)),
         "llep_grouped_ffn_backward")
+
+
+def llep_zero_absent_gradients(params: llep_plan_params, bufs: PlanBuffers, device: int, dw_gate,
+                               dw_up, dw_down, stream=None):
+    """Zeros for the experts that llep_grouped_ffn_backward leaves unwritten."""
+    D, F = dw_gate.shape[-2:]
+    _check(lib().llep_zero_absent_gradients(
+        ctypes.byref(params), ctypes.byref(bufs.struct), device, D, F, _ptr(dw_gate),
+        _ptr(dw_up), _ptr(dw_down), _stream(stream)), "llep_zero_absent_gradients")

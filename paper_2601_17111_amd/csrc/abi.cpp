@@ -383,4 +383,29 @@ int llep_grouped_ffn_backward(const llep_plan_params *params, const llep_plan_bu
   return hip_result(llep::launch_grouped_ffn_backward(a, stream), "llep_grouped_ffn_backward");
 }
 
+int llep_zero_absent_gradients(const llep_plan_params *params, const llep_plan_buffers *plan,
+                               int32_t device, int32_t D, int32_t F, float *dw_gate,
+                               float *dw_up, float *dw_down, hipStream_t stream) {
+  int rc = check_params(params);
+  if (rc != LLEP_OK) return rc;
+  if ((rc = check_plan_buffers(plan)) != LLEP_OK) return rc;
+  if ((rc = check_ffn_dims(D, F, LLEP_F32)) != LLEP_OK) return rc;
+  if (device < -1 || device >= params->P) return fail(LLEP_E_ARG, "device outside [-1, P)");
+  if (!dw_gate || !dw_up || !dw_down) return fail(LLEP_E_ARG, "a data pointer is null");
+  if (!aligned16(dw_gate) || !aligned16(dw_up) || !aligned16(dw_down))
+    return fail(LLEP_E_ARG, "data not 16-byte aligned");
+  llep::FfnBwdArgs a = {};
+  a.P = params->P;
+  a.E = params->E;
+  a.D = D;
+  a.F = F;
+  a.device = device;
+  a.groups = plan->groups;
+  a.group_begin = plan->group_begin;
+  a.dw_gate = dw_gate;
+  a.dw_up = dw_up;
+  a.dw_down = dw_down;
+  return hip_result(llep::launch_zero_absent(a, stream), "llep_zero_absent_gradients");
+}
+
 }  // extern "C"

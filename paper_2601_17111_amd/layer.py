@@ -120,8 +120,8 @@ class LLEPLayer:
             code = B.LLEP_BF16 if self.dtype == torch.bfloat16 else B.LLEP_F32
             nbytes = B.llep_grouped_ffn_backward_workspace_bytes(self.params, D, F, code)
             self.bwd_workspace = torch.empty(nbytes, dtype=torch.uint8, device=dev)
-        for w in (self.dw_gate, self.dw_up, self.dw_down):
-            w.zero_()
+        B.llep_zero_absent_gradients(self.params, self.bufs, device, self.dw_gate, self.dw_up,
+                                     self.dw_down, stream)
         B.llep_combine_backward(self.params, self.out_perm, self.pair_row, gates, dy,
                                 self.d_out_perm, self.d_gates, stream)
         B.llep_grouped_ffn_backward(self.params, self.bufs, device, self.x_perm, self.d_out_perm,

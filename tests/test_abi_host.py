@@ -206,6 +206,15 @@ def test_backward_argument_checks():
     assert call(**dict(ok, nbytes=need - 1)) == B.LLEP_E_WORKSPACE
     assert call(**dict(ok, ws=ctypes.c_void_p((1 << 24) + 64))) == B.LLEP_E_WORKSPACE
     assert call(**dict(ok, gate_up=ctypes.c_void_p(4104))) == B.LLEP_E_ARG
+    # zeros for the experts it does not write
+
+    def zero(device, D, F, dw):
+        return L.llep_zero_absent_gradients(ctypes.byref(p), ctypes.byref(bufs), device, D, F, a,
+                                            dw, a, None)
+    assert zero(4, 64, 128, a) == B.LLEP_E_ARG
+    assert zero(0, 64, 96, a) == B.LLEP_E_ARG
+    assert zero(0, 64, 128, None) == B.LLEP_E_ARG
+    assert zero(0, 64, 128, ctypes.c_void_p(4100)) == B.LLEP_E_ARG
     # more pairs than the backward's 32-bit operand offsets reach
     big = B.make_params(1 << 20, 8, 8, 4, (1 << 23) // 4)
     nb = B.llep_grouped_ffn_backward_workspace_bytes(big, 64, 128, bf)

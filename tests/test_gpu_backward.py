@@ -490,3 +490,27 @@ def test_layer_max_experts_and_devices(dev, E, P, alpha):
             a += p
     for a, t in zip(acc, (dwg, dwu, dwd)):
         assert rel_err(a, t) <= 1e-5
+
+
+@pytest.mark.parametrize("device", [-1, 0, 3])
+@pytest.mark.parametrize("loads", [(0,) * 8, (5, 0, 0, 7, 0, 0, 0, 1), (1,) * 8],
+                         ids=["none", "some", "all"])
+def test_zero_absent_gradients(dev, loads, device):
+    """Exactly the experts without a group in the range are zeroed, whole."""
+    import torch
+    from paper_2601_17111_amd import binding as B
+    E, P, D, F = 8, 4, 64, 192
+    ids = np.repeat(np.arange(E, dtype=np.int32), loads)
+    # an id out of range gives a plan without groups a pair to look at
+    ids = np.concatenate([ids, np.full(1, E, np.int32)])
+    params = B.make_params(len(ids), 1, E, P, len(ids), mode="ep")
+    bufs = B.PlanBuffers(params, dev)
+    B.llep_plan(params, torch.from_numpy(ids).to(dev), bufs)
+    dw = [torch.full((E, D, F), 3.0, device=dev) for _ in range(2)]
+    dw.append(torch.full((E, F, D), 3.0, device=dev))
+    B.llep_zero_absent_gradients(params, bufs, device, *dw)
+    torch.cuda.synchronize()
+    for e in range(E):
+        here = loads[e] > 0 and device in (-1, e // (E // P))
+        for w in dw:
+            assert (w[e] == (3.0 if here else 0.0)).all()
