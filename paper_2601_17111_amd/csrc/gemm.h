@@ -145,7 +145,9 @@ constexpr int kStages = kAhead + 1;
 // other loads stay correct (they can only wait longer). The global address
 // is a wave-uniform 64-bit base in SGPRs plus a per-lane 32-bit byte offset
 // (the instruction's saddr form), so no lane computes a 64-bit address; the
-// LDS destination (1 KB, 16 bytes per lane) starts at m0.
+// LDS destination (1 KB, 16 bytes per lane) starts at m0. kNT: the
+// non-temporal cache policy, for bytes that are read once.
+template <bool kNT = false>
 __device__ __forceinline__ void dma16(const char *base_in, int32_t voff, uint32_t lds) {
   // the base is wave-uniform by construction; readfirstlane states it (the
   // builtin returns int: both halves are widened as unsigned)
@@ -158,16 +160,28 @@ __device__ __forceinline__ void dma16(const char *base_in, int32_t voff, uint32_
   const uint32_t lds_u = uint32_t(__builtin_amdgcn_readfirstlane(lds));
   // m0 is reserved to the compiler: saved and restored inside the asm
   uint32_t saved;
-  asm volatile(
-      "s_mov_b32 %0, m0\n\t"
-      "s_mov_b32 m0, %1\n\t"
-      "s_nop 0\n\t"
-      "global_load_lds_dwordx4 %2, %3\n\t"
-      "s_nop 0\n\t"
-      "s_mov_b32 m0, %0"
-      : "=&s"(saved)
-      : "s"(lds_u), "v"(voff), "s"(base)
-      : "memory");
+  if constexpr (kNT)
+    asm volatile(
+        "s_mov_b32 %0, m0\n\t"
+        "s_mov_b32 m0, %1\n\t"
+        "s_nop 0\n\t"
+        "global_load_lds_dwordx4 %2, %3 nt\n\t"
+        "s_nop 0\n\t"
+        "s_mov_b32 m0, %0"
+        : "=&s"(saved)
+        : "s"(lds_u), "v"(voff), "s"(base)
+        : "memory");
+  else
+    asm volatile(
+        "s_mov_b32 %0, m0\n\t"
+        "s_mov_b32 m0, %1\n\t"
+        "s_nop 0\n\t"
+        "global_load_lds_dwordx4 %2, %3\n\t"
+        "s_nop 0\n\t"
+        "s_mov_b32 m0, %0"
+        : "=&s"(saved)
+        : "s"(lds_u), "v"(voff), "s"(base)
+        : "memory");
 }
 
 // LDS byte address of a shared-memory object (wave-uniform; once per kernel)

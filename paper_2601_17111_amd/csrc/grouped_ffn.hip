@@ -8,7 +8,8 @@
 //
 // This file: the tile list, the forward launcher, the float32 forward (one
 // thread per output element, reference precision, no matrix cores). The GEMM
-// kernel itself is in gemm.h, the weight packing in pack.hip.
+// kernel itself is in gemm.h, the kernel for calls of few rows in stream_ffn.hip,
+// the weight packing in pack.hip.
 #include <algorithm>
 #include <mutex>
 
@@ -500,6 +501,8 @@ hipError_t launch_grouped_ffn(const FfnArgs &a, hipStream_t stream) {
   int4 *tiles = reinterpret_cast<int4 *>(ws + L.tiles_off);
   int32_t *done = reinterpret_cast<int32_t *>(ws + L.done_off);
   void *act = ws + L.act_off;
+  if (a.dtype == LLEP_BF16 && use_stream_ffn(a.R, a.E, a.D, a.F))
+    return launch_stream_ffn(a, act, stream);
   if (a.dtype == LLEP_BF16) {
     const int grid = (cu_count() + 7) / 8 * 8;  // one workgroup per CU, XCD-balanced
     hipLaunchKernelGGL(tile_table_kernel, dim3(1), dim3(kTileTableThreads), 0, stream, a.groups,

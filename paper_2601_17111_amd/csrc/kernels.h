@@ -78,6 +78,11 @@ struct FfnArgs {
 size_t ffn_workspace_bytes(int64_t R, int32_t E, int32_t P, int32_t F,
                            llep_dtype dtype);
 hipError_t launch_grouped_ffn(const FfnArgs &a, hipStream_t stream);
+// The bf16 forward of calls of few rows (stream_ffn.hip): R pairs over all
+// devices, at most kStreamRows; act: the workspace's activation.
+constexpr int kStreamRows = 4096;
+bool use_stream_ffn(int64_t R, int32_t E, int32_t D, int32_t F);
+hipError_t launch_stream_ffn(const FfnArgs &a, void *act, hipStream_t stream);
 // Address on the current GPU of the library's LLEP_NOALLOC_SCRATCH_BYTES
 // workspace array (looked up once per GPU, then cached).
 hipError_t ffn_scratch_address(void **ptr);

@@ -1,0 +1,104 @@
+"""The weight-streaming forward (calls of few rows) against the oracle and,
+bit for bit, against the tiled kernels: group sizes at the edges of its row
+classes (16, 32, 64, 128 and 256 rows) and of its pieces (256 rows), one k-stage
+per unit, column counts that leave a workgroup's last column units empty, and
+more units than workgroups."""
+
+from fractions import Fraction
+
+import numpy as np
+import pytest
+
+import oracle
+from gpu_util import LayerRun, device, rel_err
+
+pytestmark = pytest.mark.gpu
+
+TOL_BF16 = 2e-2
+EDGES = (1, 0, 15, 16, 17, 31, 32, 33, 63, 64, 65, 0, 127, 128, 129, 255, 256, 257, 300, 512, 529)
+
+
+@pytest.fixture(scope="module")
+def dev():
+    return device()
+
+
+def _cfg(loads, D, F, P=1):
+    from paper_2601_17111_amd.synth import LayerConfig
+    return LayerConfig(f"stream-D{D}-F{F}", T=sum(loads), D=D, F=F, E=len(loads), K=1, P=P,
+                       alpha=Fraction(2), dtype="bf16", routing=("loads", tuple(loads)))
+
+
+@pytest.mark.parametrize("loads,D,F", [
+    (EDGES, 64, 64),       # one stage per unit, one column unit of four per piece
+    (EDGES, 320, 192),     # 10 output units: the last workgroup unit half empty
+    (EDGES, 1024, 576),
+    ((3,), 128, 64),       # fewer units than workgroups
+    ((1,) * 63 + (200,), 192, 640),
+], ids=["64x64", "320x192", "1024x576", "one-group", "one-hot"])
+def test_stream_forward(dev, loads, D, F):
+    import torch
+    cfg = _cfg(loads, D, F)
+    run = LayerRun(cfg, 1, dev)
+    L = run.layer
+    L.out_perm.fill_(float("nan"))
+    run.forward(-1)
+    n = cfg.T
+    out = L.out_perm[:n].clone()
+    groups = L.bufs.groups[:L.bufs.info_dict()["n_groups"]].cpu().tolist()
+    row_pair = L.row_pair[:n].cpu().numpy()
+    W = run.host_weights(range(cfg.E))
+    got = out.float().cpu().numpy()
+    for (_, e, r0, rows) in groups:
+        want = oracle.swiglu_ffn(run.inp.x[row_pair[r0:r0 + rows]].astype(np.float64),
+                                 *(w.astype(np.float64) for w in W[e]))
+        for i in range(rows):
+            assert rel_err(got[r0 + i], want[i]) <= TOL_BF16, (e, rows, i)
+    # the training forward, and the call again: the same bits; g and u are kept
+    L.ffn(run.gu, run.dn, -1, save_gate_up=True)
+    torch.cuda.synchronize()
+    assert torch.equal(L.out_perm[:n], out)
+    gu = L.gate_up[:n].clone()
+    # the same rows in a call too large for the stream (an expert of 8200 rows
+    # more): gemm.h's tiles give the same bits, g and u included
+    big = LayerRun(_cfg(tuple(loads) + (8200,), D, F), 1, dev, weights=False)
+    big.gu = torch.zeros((cfg.E + 1, 2 * F, D), dtype=torch.bfloat16, device=dev)
+    big.dn = torch.zeros((cfg.E + 1, D, F), dtype=torch.bfloat16, device=dev)
+    big.gu[:-1], big.dn[:-1] = run.gu, run.dn
+    b = big.layer
+    b.plan(big.ids)
+    b.permute(big.ids, big.gates, big.x)
+    b.x_perm[:n] = L.x_perm[:n]  # experts keep their rows' places
+    b.ffn(big.gu, big.dn, -1, save_gate_up=True)
+    torch.cuda.synchronize()
+    assert torch.equal(b.out_perm[:n], out)
+    assert torch.equal(b.gate_up[:n], gu)
+
+
+@pytest.mark.parametrize("loads,P", [
+    ((300, 2, 1, 40, 17, 0, 90, 5), 4),
+    ((487,) + (1, 0, 2) * 5, 8),            # one expert on every device: pieces of many groups
+    ((700, 3, 650, 1, 2, 0, 0, 40), 8),     # two of them, over several pieces
+    ((16, 16, 16, 16), 2),
+], ids=["spill", "hot", "two-hot", "even"])
+def test_stream_one_device_and_plans(dev, loads, P):
+    """One device's launch writes its rows alone, with the bits of the
+    all-device launch; the LLEP and EP plans give the same bits per token."""
+    import torch
+    cfg = _cfg(loads, 256, 384, P=P).with_(alpha=Fraction(1))
+    run = LayerRun(cfg, 2, dev)
+    L = run.layer
+    y = run.forward(-1).clone()
+    out = L.out_perm.clone()
+    rows = L.bufs.device_rows.cpu().tolist()
+    at = 0
+    for d in range(cfg.P):
+        L.out_perm.fill_(float("nan"))
+        L.ffn(run.gu, run.dn, d)
+        torch.cuda.synchronize()
+        assert torch.equal(L.out_perm[at:at + rows[d]], out[at:at + rows[d]])
+        assert torch.isnan(L.out_perm[:at].float()).all()
+        assert torch.isnan(L.out_perm[at + rows[d]:].float()).all()
+        at += rows[d]
+    L.set_mode("ep")
+    assert torch.equal(run.forward(-1), y)
