@@ -22,15 +22,28 @@
 
 namespace llep {
 
-__global__ __launch_bounds__(256) void rank_kernel(
-    const int32_t *__restrict__ ids, const float *__restrict__ gates, int64_t R,
-    int32_t E, int32_t max_chunks, int32_t n_tiles, const int32_t *__restrict__ rank_base,
-    const int32_t *__restrict__ chunks, const int32_t *__restrict__ chunk_row,
-    const int32_t *__restrict__ expert_chunk_begin, int32_t *__restrict__ pair_row,
-    int32_t *__restrict__ row_pair, float *__restrict__ gate_perm) {
+struct RankArgs {
+  const int32_t *ids;
+  const float *gates;
+  int64_t R;
+  int32_t E, max_chunks, n_tiles;
+  const int32_t *rank_base, *chunks, *chunk_row, *expert_chunk_begin;
+  int32_t *pair_row, *row_pair;
+  float *gate_perm;
+};
+
+// The row of pair p = 256 slice + threadIdx.x, or -1 (invalid id, no chunk,
+// past the end), and the pair's gate. 256 threads; smem: rank_lds bytes.
+__device__ __forceinline__ int32_t rank_slice(const RankArgs &a, int64_t slice, int32_t *smem,
+                                              float &gv) {
+  const int64_t R = a.R;
+  const int32_t E = a.E, max_chunks = a.max_chunks, n_tiles = a.n_tiles;
+  const int32_t *__restrict__ ids = a.ids, *__restrict__ rank_base = a.rank_base;
+  const float *__restrict__ gates = a.gates;
+  const int32_t *__restrict__ chunks = a.chunks, *__restrict__ chunk_row = a.chunk_row;
+  const int32_t *__restrict__ expert_chunk_begin = a.expert_chunk_begin;
   // LDS: per-wave bases [kRankWaves][E], then the plan's chunk table
   // (expert_chunk_begin [E+1]; start, end, first row per chunk)
-  extern __shared__ int32_t smem[];
   int32_t *wbase = smem;
   int32_t *ecb = wbase + kRankWaves * E;
   int32_t *c_start = ecb + (E + 1);
@@ -39,11 +52,11 @@ __global__ __launch_bounds__(256) void rank_kernel(
   const int tid = threadIdx.x;
   const int w = __builtin_amdgcn_readfirstlane(tid / kWave);
   const int nb = bits_for(uint32_t(E));
-  // slice blockIdx.x = slice `sub` of rank tile `tile`; wave w ranks its 64
+  // the slice is slice `sub` of rank tile `tile`; wave w ranks its 64
   // consecutive pairs
-  const int64_t tile = blockIdx.x / kRankWaves;
-  const int sub = int(blockIdx.x % kRankWaves);
-  const int64_t p = int64_t(blockIdx.x) * kRankSub + w * kWave + lane_id();
+  const int64_t tile = slice / kRankWaves;
+  const int sub = int(slice % kRankWaves);
+  const int64_t p = slice * kRankSub + w * kWave + lane_id();
   static_assert(kRankSub == kRankWaves * kWave, "a slice is one 64-pair block per wave");
   // Every global load is issued up front, before any is waited for: the
   // pair's id and gate, the slice's base counts (all of the tile's earlier
@@ -82,7 +95,7 @@ __global__ __launch_bounds__(256) void rank_kernel(
   }
   __builtin_amdgcn_sched_barrier(0);  // the loads above issue together
   uint32_t ev = uint32_t(E);  // sentinel: past the end or invalid
-  float gv = 0.0f;
+  gv = 0.0f;
   if (p < R) {
     gv = gate_raw;
     if (id_raw >= 0 && id_raw < E) ev = uint32_t(id_raw);
@@ -131,24 +144,32 @@ __global__ __launch_bounds__(256) void rank_kernel(
     }
   }
   __syncthreads();
-  // rank, locate the chunk, write the row
-  if (ev < uint32_t(E)) {
-    const int32_t r = wbase[w * E + ev] + __popcll(m & lanemask_lt());
-    int c = ecb[ev];
-    const int c1 = max(ecb[ev + 1], c);
-    while (c + 1 < c1 && r >= c_end[c]) ++c;
-    // a pair outside every chunk of its expert (a plan built from other
-    // ids) gets no row
-    const bool inside = c < c1 && r >= c_start[c] && r < c_end[c];
-    const int32_t row = inside ? c_row[c] + (r - c_start[c]) : -1;
-    pair_row[p] = row;
-    if (row >= 0 && row < R) {
-      row_pair[row] = int32_t(p);
-      gate_perm[row] = gv;
-    }
-  } else if (p < R) {
-    pair_row[p] = -1;
+  // rank, locate the chunk
+  if (ev >= uint32_t(E)) return -1;
+  const int32_t r = wbase[w * E + ev] + __popcll(m & lanemask_lt());
+  int c = ecb[ev];
+  const int c1 = max(ecb[ev + 1], c);
+  while (c + 1 < c1 && r >= c_end[c]) ++c;
+  // a pair outside every chunk of its expert (a plan built from other ids)
+  // gets no row
+  const bool inside = c < c1 && r >= c_start[c] && r < c_end[c];
+  return inside ? c_row[c] + (r - c_start[c]) : -1;
+}
+
+__device__ __forceinline__ void write_row(const RankArgs &a, int64_t p, int32_t row, float gv) {
+  if (p >= a.R) return;
+  a.pair_row[p] = row;
+  if (row >= 0 && row < a.R) {
+    a.row_pair[row] = int32_t(p);
+    a.gate_perm[row] = gv;
   }
+}
+
+__global__ __launch_bounds__(256) void rank_kernel(RankArgs a) {
+  extern __shared__ int32_t smem[];
+  float gv;
+  const int32_t row = rank_slice(a, blockIdx.x, smem, gv);
+  write_row(a, int64_t(blockIdx.x) * kRankSub + threadIdx.x, row, gv);
 }
 
 // Access choices, measured on MI355X with the gpt-oss-120b, deepseek-v3 and
@@ -260,17 +281,64 @@ void launch_gather_v(int grid, hipStream_t stream, const PermuteArgs &a, int32_t
                      a.pair_row, a.T, a.K, vecs, a.R);
 }
 
+// Small calls: both kernels in one launch. A workgroup ranks the whole slice
+// of its kSmallPairs pairs (the loads and ballots of rank_kernel; their
+// latency, not their number, is what costs) and gathers the rows of its own
+// pairs, each wave taking 1 KB pieces of the tokens' rows.
+constexpr int kSmallPairs = 4;
+constexpr int kSmallPermute = 4096;  // pairs
+
+__global__ __launch_bounds__(256) void rank_gather_kernel(RankArgs a, const i32x4 *__restrict__ x,
+                                                          i32x4 *__restrict__ x_perm, int32_t K,
+                                                          int32_t vecs) {
+  extern __shared__ int32_t smem[];
+  __shared__ int32_t rows[kRankSub];
+  static_assert(kRankSub % kSmallPairs == 0, "a workgroup's pairs are of one slice");
+  const int64_t p0 = int64_t(blockIdx.x) * kSmallPairs;
+  const int64_t slice = p0 / kRankSub;
+  float gv;
+  const int32_t row = rank_slice(a, slice, smem, gv);
+  rows[threadIdx.x] = row;
+  const int64_t p = slice * kRankSub + threadIdx.x;
+  if (p >= p0 && p < p0 + kSmallPairs) write_row(a, p, row, gv);
+  __syncthreads();
+  const int lane = lane_id(), w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int n = int(min(int64_t(kSmallPairs), a.R - p0)), at = int(p0 - slice * kRankSub);
+  for (int v0 = w * kWave; v0 < vecs; v0 += kRankWaves * kWave) {
+    const int v = v0 + lane;
+    if (v >= vecs) break;
+    // the tokens' pieces are requested together, one per token
+    i32x4 val[kSmallPairs];
+#pragma unroll
+    for (int i = 0; i < kSmallPairs; ++i)
+      if (i < n && (i == 0 || (p0 + i) % K == 0)) val[i] = x[(p0 + i) / K * vecs + v];
+#pragma unroll
+    for (int i = 0; i < kSmallPairs; ++i) {
+      if (i >= n) break;
+      if (i > 0 && (p0 + i) % K != 0) val[i] = val[i - 1];
+      const int32_t r = __builtin_amdgcn_readfirstlane(rows[at + i]);
+      if (r >= 0 && r < a.R) x_perm[int64_t(r) * vecs + v] = val[i];
+    }
+  }
+}
+
 hipError_t launch_permute(const PermuteArgs &a, hipStream_t stream) {
   if (a.R == 0) return hipSuccess;
   const size_t lds = (size_t(kRankWaves + 1) * a.E + 1 + 3 * size_t(kMaxChunks)) * sizeof(int32_t);
+  const RankArgs r = {a.ids, a.gates, a.R, a.E, a.max_chunks, a.n_tiles, a.plan.rank_base,
+                      a.plan.chunks, a.plan.chunk_row, a.plan.expert_chunk_begin, a.pair_row,
+                      a.row_pair, a.gate_perm};
+  const int32_t vecs = int32_t((int64_t(a.D) * a.elem_bytes) / 16);
+  if (a.R <= kSmallPermute) {
+    hipLaunchKernelGGL(rank_gather_kernel, dim3((a.R + kSmallPairs - 1) / kSmallPairs), dim3(256),
+                       lds, stream, r, static_cast<const i32x4 *>(a.x),
+                       static_cast<i32x4 *>(a.x_perm), a.K, vecs);
+    return hipGetLastError();
+  }
   const int64_t slices = (a.R + kRankSub - 1) / kRankSub;
-  hipLaunchKernelGGL(rank_kernel, dim3(slices), dim3(256), lds, stream, a.ids, a.gates,
-                     a.R, a.E, a.max_chunks, a.n_tiles, a.plan.rank_base, a.plan.chunks,
-                     a.plan.chunk_row, a.plan.expert_chunk_begin, a.pair_row, a.row_pair,
-                     a.gate_perm);
+  hipLaunchKernelGGL(rank_kernel, dim3(slices), dim3(256), lds, stream, r);
   hipError_t err = hipGetLastError();
   if (err != hipSuccess) return err;
-  const int32_t vecs = int32_t((int64_t(a.D) * a.elem_bytes) / 16);
   const int64_t blocks = (a.T * ((vecs + kWave - 1) / kWave) + kGatherWaves - 1) / kGatherWaves;
   const int grid = int(blocks < kGatherGrid ? blocks : kGatherGrid);
   launch_gather_v<1>(grid, stream, a, vecs);

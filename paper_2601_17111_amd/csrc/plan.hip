@@ -90,7 +90,11 @@ __global__ __launch_bounds__(256) void hist_kernel(const int32_t *__restrict__ i
 // ---------------------------------------------------------------------------
 
 constexpr int kPlanThreads = 1024;
-constexpr int kPlanWaves = kPlanThreads / kWave;
+// Calls of at most kPlanHistPairs pairs are counted by the plan kernel itself
+// (one launch instead of two, 5 us), with kSmallPlanThreads threads when the
+// experts allow it (cheaper barriers).
+constexpr int kPlanHistPairs = 4096;
+constexpr int kSmallPlanThreads = 256;
 
 // Tile counts of one expert column that a thread keeps in registers
 // between the two passes of the scan (and loads at once in either pass).
@@ -177,7 +181,12 @@ __device__ void wave_exclusive_scan(const int32_t *in, int n, int32_t *out,
   }
 }
 
-__global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
+// NT threads (at least E, and at least four waves); kHist: the kernel counts
+// the pairs itself (R <= kPlanHistPairs), otherwise hist_kernel has.
+template <int NT, bool kHist>
+__global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
+  constexpr int kPlanThreads = NT, kPlanWaves = NT / kWave;
+  static_assert(kPlanWaves >= 4, "three scans beside wave 0");
   __shared__ PlanShared s;
   const int tid = threadIdx.x;
   const int wave = tid / kWave;
@@ -185,12 +194,78 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
   const int nt = a.n_tiles;
   int32_t *rb = a.buf.rank_base;
 
+  for (int e = tid; e <= E; e += NT) {
+    s.e_cnt[e] = 0;
+    s.e_xfers[e] = 0;
+  }
+  if (tid <= P) {
+    s.d_chunks[tid] = 0;
+    s.d_groups[tid] = 0;
+    s.dev_rows[tid] = 0;
+  }
+  // ---- 1. (kHist) counts per slice of kRankSub pairs, per-tile bases, loads ----
+  if constexpr (kHist) {
+    extern __shared__ int32_t cnt[];  // [slices][E]
+    const int lane = lane_id();
+    const int nb = bits_for(uint32_t(E));
+    const int R = int(a.R), n_slices = nt * kRankWaves;
+    // every id is requested before the counts are cleared (a pair past the
+    // end reads the last pair's id and is dropped)
+    constexpr int kPer = kPlanHistPairs / NT;
+    int32_t raw[kPer];
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+      raw[j] = 0;
+      if (j * NT < R) raw[j] = a.ids[min(j * NT + tid, R - 1)];
+    }
+    for (int i = tid; i < n_slices * E; i += NT) cnt[i] = 0;
+    __syncthreads();
+    int bad = 0;
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+      const int p0 = j * NT + tid - lane;  // the wave's 64 pairs are of one slice
+      if (p0 >= R) break;
+      const bool in = p0 + lane < R;
+      const bool ok = raw[j] >= 0 && raw[j] < E;
+      if (in && !ok) bad = 1;
+      const uint32_t e = in && ok ? uint32_t(raw[j]) : uint32_t(E);  // sentinel
+      const uint64_t m = match_any(e, nb);
+      // one leader lane per expert value; other waves of the slice add too
+      if (e < uint32_t(E) && (m & lanemask_lt()) == 0)
+        atomicAdd(&cnt[(p0 / kRankSub) * E + e], int(__popcll(m)));
+    }
+    bad = __syncthreads_or(bad);
+    int32_t *slices = rb + int64_t(nt) * (E + 1);
+    for (int e = tid; e < E; e += NT) {
+      int32_t run = 0;
+      for (int t = 0; t < nt; ++t) {
+        rb[int64_t(t) * E + e] = run;
+#pragma unroll
+        for (int v = 0; v < kRankWaves; ++v) {
+          const int32_t c = cnt[(t * kRankWaves + v) * E + e];
+          slices[(t * kRankWaves + v) * E + e] = c;
+          run += c;
+        }
+      }
+      s.loads[e] = run;
+      a.buf.loads[e] = run;
+    }
+    if (tid == 0) {
+      s.status = bad ? LLEP_STATUS_BAD_EXPERT_ID : 0;
+      s.n_chunks = 0;
+      s.forced = 0;
+      s.bypass = 0;
+      s.n_groups = 0;
+      s.n_xfers = 0;
+    }
+    __syncthreads();
+  }
   // ---- 1. scan tile counts: per-tile exclusive bases, and loads ----------
   // Each expert's column of tile counts is split into G segments. A segment
   // of up to kScanHold tiles is loaded at once and kept in registers for the
   // second pass, so the scan costs one memory round trip (plus the stores);
   // longer segments take two passes of kScanHold loads at a time.
-  {
+  if constexpr (!kHist) {
     const int G = kPlanThreads / E;  // E <= 512: G >= 2
     const int e = tid % E, grp = tid / E;
     const int seg = (nt + G - 1) / G;
@@ -223,15 +298,6 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
       }
     }
     s.part[tid] = sum;
-    if (tid <= E) {
-      s.e_cnt[tid] = 0;
-      s.e_xfers[tid] = 0;
-    }
-    if (tid <= P) {
-      s.d_chunks[tid] = 0;
-      s.d_groups[tid] = 0;
-      s.dev_rows[tid] = 0;
-    }
     bad = __syncthreads_or(bad);
     if (grp < G) {
       int32_t run = 0;
@@ -268,8 +334,8 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
       s.n_xfers = 0;
     }
     __syncthreads();
+    for (int e = tid; e < E; e += kPlanThreads) a.buf.loads[e] = s.loads[e];
   }
-  for (int e = tid; e < E; e += kPlanThreads) a.buf.loads[e] = s.loads[e];
 
   // ---- 2. lambda test (Alg. 4): max(l) * E < lambda * sum(l) ------------
   bool use_ep = a.mode == LLEP_MODE_EP || P == 1;
@@ -565,14 +631,22 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
 }
 
 hipError_t launch_plan(const PlanArgs &a, hipStream_t stream) {
-  if (a.n_tiles > 0) {
-    hipLaunchKernelGGL(hist_kernel, dim3(a.n_tiles), dim3(256),
-                       size_t(kRankWaves) * a.E * sizeof(int32_t), stream, a.ids, a.R, a.E,
-                       a.n_tiles, a.buf.rank_base);
-    hipError_t err = hipGetLastError();
-    if (err != hipSuccess) return err;
+  if (a.R <= kPlanHistPairs) {
+    const size_t lds = size_t(a.n_tiles) * kRankWaves * a.E * sizeof(int32_t);
+    if (a.E <= kSmallPlanThreads)
+      hipLaunchKernelGGL((plan_kernel<kSmallPlanThreads, true>), dim3(1), dim3(kSmallPlanThreads),
+                         lds, stream, a);
+    else
+      hipLaunchKernelGGL((plan_kernel<kPlanThreads, true>), dim3(1), dim3(kPlanThreads), lds,
+                         stream, a);
+    return hipGetLastError();
   }
-  hipLaunchKernelGGL(plan_kernel, dim3(1), dim3(kPlanThreads), 0, stream, a);
+  hipLaunchKernelGGL(hist_kernel, dim3(a.n_tiles), dim3(256),
+                     size_t(kRankWaves) * a.E * sizeof(int32_t), stream, a.ids, a.R, a.E,
+                     a.n_tiles, a.buf.rank_base);
+  const hipError_t err = hipGetLastError();
+  if (err != hipSuccess) return err;
+  hipLaunchKernelGGL((plan_kernel<kPlanThreads, false>), dim3(1), dim3(kPlanThreads), 0, stream, a);
   return hipGetLastError();
 }
 
