@@ -90,11 +90,11 @@ __global__ __launch_bounds__(256) void hist_kernel(const int32_t *__restrict__ i
 // ---------------------------------------------------------------------------
 
 constexpr int kPlanThreads = 1024;
-// Calls of at most kPlanHistPairs pairs are counted by the plan kernel itself
-// (one launch instead of two, 5 us), with kSmallPlanThreads threads when the
-// experts allow it (cheaper barriers).
+constexpr int kPlanWaves = kPlanThreads / kWave;
+// Calls of at most kPlanHistPairs pairs are counted by the plan kernel itself:
+// one launch instead of two (5 us). (256 or 512 threads for these calls: 0.2
+// us faster for one token, 2-5 us slower from 64 tokens on.)
 constexpr int kPlanHistPairs = 4096;
-constexpr int kSmallPlanThreads = 256;
 
 // Tile counts of one expert column that a thread keeps in registers
 // between the two passes of the scan (and loads at once in either pass).
@@ -181,12 +181,10 @@ __device__ void wave_exclusive_scan(const int32_t *in, int n, int32_t *out,
   }
 }
 
-// NT threads (at least E, and at least four waves); kHist: the kernel counts
-// the pairs itself (R <= kPlanHistPairs), otherwise hist_kernel has.
-template <int NT, bool kHist>
-__global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
-  constexpr int kPlanThreads = NT, kPlanWaves = NT / kWave;
-  static_assert(kPlanWaves >= 4, "three scans beside wave 0");
+// kHist: the kernel counts the pairs itself (R <= kPlanHistPairs), otherwise
+// hist_kernel has.
+template <bool kHist>
+__global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs a) {
   __shared__ PlanShared s;
   const int tid = threadIdx.x;
   const int wave = tid / kWave;
@@ -194,9 +192,9 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
   const int nt = a.n_tiles;
   int32_t *rb = a.buf.rank_base;
 
-  for (int e = tid; e <= E; e += NT) {
-    s.e_cnt[e] = 0;
-    s.e_xfers[e] = 0;
+  if (tid <= E) {
+    s.e_cnt[tid] = 0;
+    s.e_xfers[tid] = 0;
   }
   if (tid <= P) {
     s.d_chunks[tid] = 0;
@@ -211,19 +209,19 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
     const int R = int(a.R), n_slices = nt * kRankWaves;
     // every id is requested before the counts are cleared (a pair past the
     // end reads the last pair's id and is dropped)
-    constexpr int kPer = kPlanHistPairs / NT;
+    constexpr int kPer = kPlanHistPairs / kPlanThreads;
     int32_t raw[kPer];
 #pragma unroll
     for (int j = 0; j < kPer; ++j) {
       raw[j] = 0;
-      if (j * NT < R) raw[j] = a.ids[min(j * NT + tid, R - 1)];
+      if (j * kPlanThreads < R) raw[j] = a.ids[min(j * kPlanThreads + tid, R - 1)];
     }
-    for (int i = tid; i < n_slices * E; i += NT) cnt[i] = 0;
+    for (int i = tid; i < n_slices * E; i += kPlanThreads) cnt[i] = 0;
     __syncthreads();
     int bad = 0;
 #pragma unroll
     for (int j = 0; j < kPer; ++j) {
-      const int p0 = j * NT + tid - lane;  // the wave's 64 pairs are of one slice
+      const int p0 = j * kPlanThreads + tid - lane;  // the wave's 64 pairs are of one slice
       if (p0 >= R) break;
       const bool in = p0 + lane < R;
       const bool ok = raw[j] >= 0 && raw[j] < E;
@@ -236,7 +234,7 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
     }
     bad = __syncthreads_or(bad);
     int32_t *slices = rb + int64_t(nt) * (E + 1);
-    for (int e = tid; e < E; e += NT) {
+    for (int e = tid; e < E; e += kPlanThreads) {
       int32_t run = 0;
       for (int t = 0; t < nt; ++t) {
         rb[int64_t(t) * E + e] = run;
@@ -633,12 +631,7 @@ __global__ __launch_bounds__(NT) void plan_kernel(PlanArgs a) {
 hipError_t launch_plan(const PlanArgs &a, hipStream_t stream) {
   if (a.R <= kPlanHistPairs) {
     const size_t lds = size_t(a.n_tiles) * kRankWaves * a.E * sizeof(int32_t);
-    if (a.E <= kSmallPlanThreads)
-      hipLaunchKernelGGL((plan_kernel<kSmallPlanThreads, true>), dim3(1), dim3(kSmallPlanThreads),
-                         lds, stream, a);
-    else
-      hipLaunchKernelGGL((plan_kernel<kPlanThreads, true>), dim3(1), dim3(kPlanThreads), lds,
-                         stream, a);
+    hipLaunchKernelGGL(plan_kernel<true>, dim3(1), dim3(kPlanThreads), lds, stream, a);
     return hipGetLastError();
   }
   hipLaunchKernelGGL(hist_kernel, dim3(a.n_tiles), dim3(256),
@@ -646,7 +639,7 @@ hipError_t launch_plan(const PlanArgs &a, hipStream_t stream) {
                      a.n_tiles, a.buf.rank_base);
   const hipError_t err = hipGetLastError();
   if (err != hipSuccess) return err;
-  hipLaunchKernelGGL((plan_kernel<kPlanThreads, false>), dim3(1), dim3(kPlanThreads), 0, stream, a);
+  hipLaunchKernelGGL(plan_kernel<false>, dim3(1), dim3(kPlanThreads), 0, stream, a);
   return hipGetLastError();
 }
 
