@@ -14,7 +14,7 @@ BUILD_DIR = os.path.join(PKG, "_build")
 LIB_PATH = os.path.join(PKG, "libllep.so")
 
 SOURCES = ["plan.hip", "permute.hip", "pack.hip", "stream_ffn.hip", "grouped_ffn.hip",
-           "grouped_ffn_bwd.hip", "abi.cpp"]
+           "grouped_ffn_bwd.hip", "ffn_f32.hip", "abi.cpp"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"

@@ -1065,30 +1065,6 @@ __host__ __device__ __forceinline__ int64_t packed_index(int n, int k, int K) {
   return (int64_t(n >> 4) * (K >> 5) + (k >> 5)) * 512 + (n & 15) * 32 + (k & 31);
 }
 
-// ---------------------------------------------------------------------------
-// float32 path helpers: the rows and groups of a launch's device range
-// ---------------------------------------------------------------------------
-
-__device__ __forceinline__ void device_range(const int32_t *groups, const int32_t *group_begin,
-                                             int device, int P, int &lo, int &hi, int &row_first,
-                                             int &rows) {
-  lo = device < 0 ? group_begin[0] : group_begin[device];
-  hi = device < 0 ? group_begin[P] : group_begin[device + 1];
-  row_first = lo < hi ? groups[4 * lo + 2] : 0;
-  rows = lo < hi ? groups[4 * (hi - 1) + 2] + groups[4 * (hi - 1) + 3] - row_first : 0;
-}
-
-__device__ __forceinline__ int group_of_row(const int32_t *groups, int lo, int hi, int row) {
-  // last group g in [lo, hi) with row_start <= row
-  int a = lo, b = hi - 1;
-  while (a < b) {
-    const int mid = (a + b + 1) >> 1;
-    if (groups[4 * mid + 2] <= row) a = mid;
-    else b = mid - 1;
-  }
-  return a;
-}
-
 // number of compute units of the current device (256 if it cannot be read)
 inline int cu_count() {
   int dev = 0, n = 0;

@@ -6,10 +6,10 @@
 //   act = silu(X Wg_e) * (X Wu_e)      GEMM 1, SwiGLU fused in the epilogue
 //   out = act Wd_e                      GEMM 2
 //
-// This file: the tile list, the forward launcher, the float32 forward (one
-// thread per output element, reference precision, no matrix cores). The GEMM
-// kernel itself is in gemm.h, the kernel for calls of few rows in stream_ffn.hip,
-// the weight packing in pack.hip.
+// This file: the tile list, the single-launch forward and the launcher. The
+// GEMM itself is in gemm.h, the kernel for calls of few rows in
+// stream_ffn.hip, the float32 path in ffn_f32.hip, the weight packing in
+// pack.hip.
 #include <algorithm>
 #include <mutex>
 
@@ -127,56 +127,6 @@ hipError_t launch_tile_table(const int32_t *groups, const int32_t *group_begin, 
   hipLaunchKernelGGL(tile_table_kernel, dim3(1), dim3(kTileTableThreads), 0, stream, groups,
                      group_begin, cap, device, P, kTileM, tiles, n_tiles, nullptr, nullptr);
   return hipGetLastError();
-}
-
-// ---------------------------------------------------------------------------
-// float32 forward
-// ---------------------------------------------------------------------------
-
-__global__ __launch_bounds__(256) void ffn_f32_gate_up_kernel(
-    const float *__restrict__ x_perm, const float *__restrict__ wgu, float *__restrict__ act,
-    float *__restrict__ gu_save, const int32_t *__restrict__ groups,
-    const int32_t *__restrict__ group_begin, int32_t device, int32_t P, int32_t D, int32_t F) {
-  int lo, hi, row_first, rows;
-  device_range(groups, group_begin, device, P, lo, hi, row_first, rows);
-  const int64_t total = int64_t(rows) * F;
-  for (int64_t u = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; u < total;
-       u += int64_t(gridDim.x) * blockDim.x) {
-    const int row = row_first + int(u / F), f = int(u % F);
-    const int e = groups[4 * group_of_row(groups, lo, hi, row) + 1];
-    const float *xr = x_perm + int64_t(row) * D;
-    const int pg = 64 * (f / 32) + (f % 32);
-    const float *we = wgu + int64_t(e) * 2 * F * D;
-    float gs = 0.0f, us = 0.0f;
-    for (int d = 0; d < D; ++d) {
-      gs = fmaf(xr[d], we[packed_index(pg, d, D)], gs);
-      us = fmaf(xr[d], we[packed_index(pg + 32, d, D)], us);
-    }
-    act[int64_t(row) * F + f] = gs / (1.0f + expf(-gs)) * us;
-    if (gu_save) {
-      gu_save[int64_t(row) * 2 * F + pg] = gs;
-      gu_save[int64_t(row) * 2 * F + pg + 32] = us;
-    }
-  }
-}
-
-__global__ __launch_bounds__(256) void ffn_f32_down_kernel(
-    const float *__restrict__ act, const float *__restrict__ wd, float *__restrict__ out,
-    const int32_t *__restrict__ groups, const int32_t *__restrict__ group_begin, int32_t device,
-    int32_t P, int32_t D, int32_t F) {
-  int lo, hi, row_first, rows;
-  device_range(groups, group_begin, device, P, lo, hi, row_first, rows);
-  const int64_t total = int64_t(rows) * D;
-  for (int64_t u = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; u < total;
-       u += int64_t(gridDim.x) * blockDim.x) {
-    const int row = row_first + int(u / D), c = int(u % D);
-    const int e = groups[4 * group_of_row(groups, lo, hi, row) + 1];
-    const float *ar = act + int64_t(row) * F;
-    const float *we = wd + int64_t(e) * D * F;
-    float s = 0.0f;
-    for (int f = 0; f < F; ++f) s = fmaf(ar[f], we[packed_index(c, f, F)], s);
-    out[int64_t(row) * D + c] = s;
-  }
 }
 
 // ---------------------------------------------------------------------------
@@ -569,17 +519,7 @@ hipError_t launch_grouped_ffn(const FfnArgs &a, hipStream_t stream) {
                          dim3(grid), dim3(NT), 0, stream, g2);
     return hipGetLastError();
   }
-  hipLaunchKernelGGL(ffn_f32_gate_up_kernel, dim3(1024), dim3(256), 0, stream,
-                     static_cast<const float *>(a.x_perm), static_cast<const float *>(a.w_gate_up),
-                     static_cast<float *>(act), static_cast<float *>(a.gate_up_out), a.groups,
-                     a.group_begin, a.device, a.P, a.D, a.F);
-  hipError_t err = hipGetLastError();
-  if (err != hipSuccess) return err;
-  hipLaunchKernelGGL(ffn_f32_down_kernel, dim3(1024), dim3(256), 0, stream,
-                     static_cast<const float *>(act), static_cast<const float *>(a.w_down),
-                     static_cast<float *>(a.out_perm), a.groups, a.group_begin, a.device, a.P,
-                     a.D, a.F);
-  return hipGetLastError();
+  return launch_ffn_f32(a, act, stream);
 }
 
 // ---------------------------------------------------------------------------

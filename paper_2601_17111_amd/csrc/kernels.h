@@ -83,6 +83,12 @@ hipError_t launch_grouped_ffn(const FfnArgs &a, hipStream_t stream);
 constexpr int kStreamRows = 4096;
 bool use_stream_ffn(int64_t R, int32_t E, int32_t D, int32_t F);
 hipError_t launch_stream_ffn(const FfnArgs &a, void *act, hipStream_t stream);
+// The float32 forward and backward (ffn_f32.hip); act [R][F] and dgu [R][2F]
+// by x_perm row, in the workspace.
+struct FfnBwdArgs;
+hipError_t launch_ffn_f32(const FfnArgs &a, void *act, hipStream_t stream);
+hipError_t launch_ffn_f32_backward(const FfnBwdArgs &a, float *dgu, float *act,
+                                   hipStream_t stream);
 // Address on the current GPU of the library's LLEP_NOALLOC_SCRATCH_BYTES
 // workspace array (looked up once per GPU, then cached).
 hipError_t ffn_scratch_address(void **ptr);
