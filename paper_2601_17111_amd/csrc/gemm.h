@@ -51,25 +51,11 @@ constexpr int kGroupM = LLEP_GROUP_M;  // m-tiles per super-row of the tile orde
 // bf16 MFMA grouped GEMM: C[m][n] = sum_k A[m][k] B_e[n][k]
 // ---------------------------------------------------------------------------
 
-// Epilogues: the forward projections (plain bf16 C, or SwiGLU of gate/up
-// column pairs; a training forward also stores the gate / up values), the
-// SwiGLU backward (C = d act; reads the gate / up values, writes their
-// gradients and the activation), and the backward's
-// multi-problem launch: the input-gradient tiles (plain bf16 C) together with
-// the tiles of the two weight gradients (fp32, per expert; gate/up columns
-// de-interleaved), handed out through a work counter.
-enum Epilogue : int { kEpiPlain = 0, kEpiSwiglu = 1, kEpiSwigluBwd = 2, kEpiBwdMulti = 3 };
-
-// A weight-gradient problem: per expert e, C_e[m][n] = sum over the k-segment
-// of e of A[m][k] B[n][k], both operands blocked over the whole k range.
-struct WgProblem {
-  const uint16_t *A, *B;  // blocked [M][kmax], [N][kmax]
-  int64_t blk_stride;     // bytes per 16-row block of A and B (kmax / 32 KB)
-  float *C, *C2;          // C [E][M][N] fp32; gate/up problem: gate into C, up into C2,
-                          // each [E][M][N / 2]
-  int64_t expert_stride;  // elements per expert of C (and C2)
-  int32_t M, N, gate_up;
-};
+// Epilogues: plain bf16 C (the forward's down projection, the backward's g, u
+// and input gradient), SwiGLU of gate/up column pairs (a training forward also
+// stores the gate / up values), and the SwiGLU backward (C = d act; reads the
+// gate / up values, writes their gradients and the activation).
+enum Epilogue : int { kEpiPlain = 0, kEpiSwiglu = 1, kEpiSwigluBwd = 2 };
 
 struct GemmArgs {
   const uint16_t *A;
@@ -89,24 +75,10 @@ struct GemmArgs {
   // null: not written
   uint16_t *gu_save;
   // SwiGLU backward: reads the gate / up values (row-major by x_perm row,
-  // ld 2F, interleaved per 32); writes [d g | d u] blocked over padded rows
-  // (C) and [d g | d u] and the activation transposed into the
-  // weight-gradient layout: blocks of 16 columns x 32 rows over
-  // [columns][kmax], the rows of group g starting at kbase[g]
+  // ld 2F, interleaved per 32); writes [d g | d u] (C) and the activation
+  // (act), both blocked over padded rows
   const uint16_t *GU;
-  uint16_t *dgu_t, *act_t;
-  const int32_t *kbase;
-  int64_t kmax;
-  // multi-problem backward launch: weight-gradient tiles of the experts in
-  // wg_experts (longest k-segment first), problem wp[0] then wp[1] per
-  // expert, and the tiles of the main problem, handed out longest first
-  // (LaunchSched::decode); tiles past the first gridDim come from the
-  // counter *queue (zero before the launch)
-  WgProblem wp[2];
-  const int4 *wg_experts;  // (expert, first k-slice, k-slices, 0)
-  const int32_t *n_wg;
-  const int32_t *n_wg_long;  // the first of them whose tiles are at least as long as a main tile
-  int32_t *queue;
+  uint16_t *act;
 };
 
 
@@ -231,9 +203,8 @@ __device__ __forceinline__ void swap_halves(uint32_t &lo, uint32_t &hi) {
 }
 
 struct TileCoord {
-  int e, row0, prow0, m0, rows_valid, n0, cols_valid, k0, nk, grp;
-  int p, N;  // problem (0: the main one, 1 / 2: wp[0] / wp[1]) and its columns
-  int mt;    // entry of the tile list (the forward's single-launch form)
+  int e, row0, prow0, m0, rows_valid, n0, cols_valid, nk;
+  int mt;  // entry of the tile list (the forward's single-launch form)
 };
 
 template <int BM, int BN>
@@ -246,7 +217,6 @@ __device__ __forceinline__ bool decode_tile(const GemmArgs &g, int u, int n_mt, 
   const int nt = rem / gm;
   const int4 te = g.tiles[sr * kGroupM + rem % gm];
   const int32_t *gr = g.groups + 4 * te.x;
-  t.grp = te.x;
   t.e = gr[1];
   t.row0 = gr[2];
   t.prow0 = te.z;
@@ -254,39 +224,8 @@ __device__ __forceinline__ bool decode_tile(const GemmArgs &g, int u, int n_mt, 
   t.rows_valid = min(BM, gr[3] - t.m0);
   t.n0 = nt * BN;
   t.cols_valid = min(BN, g.N - t.n0);
-  t.k0 = 0;
   t.nk = g.Kdim / kSK;
-  t.p = 0;
-  t.N = g.N;
   return true;
-}
-
-// weight-gradient tile u < n_exp * (tiles of wp[0] + tiles of wp[1]):
-// expert-major, then problem, then m-tile, then n-tile; the contraction runs
-// over the expert's k-segment
-template <int BM, int BN>
-__device__ __forceinline__ void decode_tile_wg(const GemmArgs &g, int u, int per0, int per1,
-                                               TileCoord &t) {
-  const int i = u / (per0 + per1);
-  int rem = u - i * (per0 + per1);
-  const bool second = rem >= per0;
-  rem -= second ? per0 : 0;
-  const int M = second ? g.wp[1].M : g.wp[0].M;
-  const int N = second ? g.wp[1].N : g.wp[0].N;
-  const int n_nt = (N + BN - 1) / BN;
-  const int4 we = g.wg_experts[i];
-  t.grp = 0;
-  t.e = we.x;
-  t.row0 = 0;
-  t.prow0 = 0;
-  t.m0 = (rem / n_nt) * BM;
-  t.rows_valid = min(BM, M - t.m0);
-  t.n0 = (rem % n_nt) * BN;
-  t.cols_valid = min(BN, N - t.n0);
-  t.k0 = we.y;
-  t.nk = we.z;
-  t.p = second ? 2 : 1;
-  t.N = N;
 }
 
 // Byte size of the LDS ring of a 256 x BN tile (kStages stages of A and B
@@ -305,62 +244,35 @@ constexpr uint32_t ring_bytes() {
 //              loop ends after the current tile;
 //   done(c, more)  all threads, after tile c's epilogue (its stores issued;
 //              more: another tile of this loop follows);
+//   kOpaqueLane  whether the lane index is hidden from the compiler's hoisting;
 //   kCoherentC whether C is stored device-coherent (read by other tiles of
 //              the same launch).
 //
 // LaunchSched serves a launch of one problem: tiles (it * G + slot) of the
-// tile order, or, in the backward's multi-problem launch, the weight-gradient
-// tiles and then the main problem's tiles from the work counter g.queue (the
-// first G implicitly: tile blockIdx-derived slot).
-template <int BM, int BN, bool kMulti>
+// tile order.
+template <int BM, int BN>
 struct LaunchSched {
+  static constexpr bool kOpaqueLane = false;
   static constexpr bool kCoherentC = false;  // C is read only by later launches
   GemmArgs g;  // a copy (no reference to the kernel argument: its fields
                // then stay in registers)
-  int n_mt, n_nt, per0, per1, n_wgt, n_long, G, slot, it;
-  int32_t *s_next;  // LDS: the next tile from the counter (multi-problem launch)
+  int n_mt, n_nt, G, slot, it;
 
-  __device__ __forceinline__ LaunchSched(const GemmArgs g_, int32_t *s_next_) : g(g_), s_next(s_next_) {
+  __device__ __forceinline__ explicit LaunchSched(const GemmArgs g_) : g(g_) {
     n_mt = *g.n_mtiles;
     n_nt = (g.N + BN - 1) / BN;
-    per0 = per1 = n_wgt = n_long = 0;
-    if constexpr (kMulti) {
-      per0 = ((g.wp[0].M + BM - 1) / BM) * ((g.wp[0].N + BN - 1) / BN);
-      per1 = ((g.wp[1].M + BM - 1) / BM) * ((g.wp[1].N + BN - 1) / BN);
-      n_wgt = *g.n_wg * (per0 + per1);
-      n_long = *g.n_wg_long * (per0 + per1);
-    }
     G = gridDim.x;  // a multiple of 8
     // the hardware deals workgroups round-robin over the 8 XCDs: slot gives
     // each XCD a contiguous block of G / 8 tiles of every round
     slot = (blockIdx.x % 8) * (G / 8) + blockIdx.x / 8;
     it = 0;
   }
-  // The multi-problem launch hands its tiles out longest first, so that the
-  // last ones to start are short and the workgroups finish together: the
-  // weight-gradient tiles of the experts whose k-segment is at least as long
-  // as a main tile's, then the main tiles, then the other weight-gradient
-  // tiles.
-  __device__ __forceinline__ bool decode(int u, TileCoord &c) const {
-    if constexpr (kMulti) {
-      const int n_main = n_mt * n_nt;
-      if (u < n_long || (u >= n_long + n_main && u < n_wgt + n_main)) {
-        decode_tile_wg<BM, BN>(g, u < n_long ? u : u - n_main, per0, per1, c);
-        return true;
-      }
-      return decode_tile<BM, BN>(g, u - n_long, n_mt, n_nt, c);
-    }
-    return decode_tile<BM, BN>(g, u, n_mt, n_nt, c);
+  __device__ __forceinline__ bool first(TileCoord &t) {
+    return decode_tile<BM, BN>(g, slot, n_mt, n_nt, t);
   }
-  __device__ __forceinline__ bool first(TileCoord &t) { return decode(slot, t); }
-  __device__ __forceinline__ void request() {
-    if (kMulti && threadIdx.x == 0) *s_next = atomicAdd(g.queue, 1) + G;
-  }
+  __device__ __forceinline__ void request() {}
   __device__ __forceinline__ bool next(TileCoord &t) {
-    ++it;
-    // (the value every thread reads from LDS is the same: stated, so the
-    // tile's coordinates stay in scalar registers)
-    return decode(kMulti ? __builtin_amdgcn_readfirstlane(*s_next) : it * G + slot, t);
+    return decode_tile<BM, BN>(g, ++it * G + slot, n_mt, n_nt, t);
   }
   __device__ __forceinline__ void done(const TileCoord &, bool) {}
 };
@@ -380,7 +292,6 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs g, char *smem, TileCoo
   constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;
   constexpr int TM = WM / 32, TN = WN / 32;
   constexpr bool kSwiglu = kEpi == kEpiSwiglu;
-  constexpr bool kMulti = kEpi == kEpiBwdMulti;
   // DMA blocks (16 rows each) per stage, dealt round-robin over the waves:
   // every wave has A_PER_WAVE A blocks and B_FULL B blocks, the first B_REM
   // waves one B block more. Waits count the PER_STAGE instructions every
@@ -408,7 +319,10 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs g, char *smem, TileCoo
     return reinterpret_cast<const uint16_t *>(smem + st * STAGE_BYTES + A_STAGE_BYTES);
   };
 
-  const int lane = threadIdx.x & 63;
+  // (kOpaqueLane: what is derived from it then holds no register in the other
+  // tile loop of the launch)
+  int lane = threadIdx.x & 63;
+  if constexpr (Sched::kOpaqueLane) asm volatile("" : "+v"(lane));
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave / WAVES_N, wn = wave % WAVES_N;
   const int64_t lda_b = g.lda * 2;
@@ -426,26 +340,15 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs g, char *smem, TileCoo
     asm volatile("" : "+v"(ln));
     const int kc_load = (ln & 3) ^ ((ln >> 4) & 3);
     const int32_t blk_lane = (ln >> 2) * 64 + kc_load * 16;
-    const uint16_t *Ap = g.A, *Bp = g.B;
-    int64_t a_bs = g.a_blk_stride, b_es = g.b_expert_stride, b_bs = g.b_blk_stride;
-    if (kMulti && c.p != 0) {
-      const bool second = c.p == 2;
-      Ap = second ? g.wp[1].A : g.wp[0].A;
-      Bp = second ? g.wp[1].B : g.wp[0].B;
-      a_bs = b_bs = second ? g.wp[1].blk_stride : g.wp[0].blk_stride;
-      b_es = 0;
-    }
     // rows (columns) past the tile's valid ones re-read its last valid row
     // (block), so every address stays in bounds
     if (kABlocked) {
-      // padded rows of the group; weight gradients: rows of the expert's
-      // M x K operand (prow0 = 0), from its k-segment on
-      const int64_t rb0 = (c.prow0 + c.m0) >> 4;
-      Ab = reinterpret_cast<const char *>(Ap) + rb0 * a_bs + int64_t(c.k0) * 1024;
+      const int64_t rb0 = (c.prow0 + c.m0) >> 4;  // padded rows of the group
+      Ab = reinterpret_cast<const char *>(g.A) + rb0 * g.a_blk_stride;
 #pragma unroll
       for (int j = 0; j < A_PER_WAVE; ++j) {
         const int rb = min(wave + NWD * j, (c.rows_valid - 1) >> 4);
-        offA[j] = int32_t(rb * a_bs + blk_lane);
+        offA[j] = int32_t(rb * g.a_blk_stride + blk_lane);
       }
     } else {
       Ab = reinterpret_cast<const char *>(g.A) + int64_t(c.row0 + c.m0) * lda_b;
@@ -458,12 +361,12 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs g, char *smem, TileCoo
         offA[j] = int32_t(__umul24(uint32_t(r), lda_b32) + uint32_t(kc_load * 16));
       }
     }
-    Bb = reinterpret_cast<const char *>(Bp) + int64_t(c.e) * b_es * 2 + (c.n0 >> 4) * b_bs +
-         int64_t(c.k0) * 1024;
+    Bb = reinterpret_cast<const char *>(g.B) + int64_t(c.e) * g.b_expert_stride * 2 +
+         (c.n0 >> 4) * g.b_blk_stride;
 #pragma unroll
     for (int j = 0; j < B_SLOTS; ++j) {
       const int nb = min(wave + NWD * j, (c.cols_valid - 1) >> 4);
-      offB[j] = int32_t(nb * b_bs + blk_lane);
+      offB[j] = int32_t(nb * g.b_blk_stride + blk_lane);
     }
   };
   // request slice kt into stage st: 64 B per row along K for a row-major A,
@@ -788,18 +691,12 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs g, char *smem, TileCoo
       // C = d act for activation columns f. With g = gate, u = up (saved by
       // the forward or recomputed; row-major by x_perm row, gate f at column
       // 64 (f / 32) + f % 32, up 32 further): d gate = d act u silu'(g) and
-      // d up = d act silu(g) go to C in the same layout (for dX), and d gate,
-      // d up and act = silu(g) u go transposed to the weight-gradient layout:
-      // a 32-row piece of the group is one 32-deep k-block there, staged in
-      // LDS as [column][row] (2 KB per 32 x 32 output) and stored as two
-      // 1 KB blocks. Rows past the group's end are written as zeros.
+      // d up = d act silu(g) go to C in the same column order and act =
+      // silu(g) u to g.act, both in 16 x 32 blocks over padded rows, which the
+      // input-gradient and weight-gradient tiles read alike. All 16-byte runs.
       static_assert(kCBlocked, "gate/up gradients are blocked over padded rows");
-      static_assert(3 * 2048 <= STAGING, "staging");
       const int F = int(g.ldc);
       const int gu_blocks = (2 * F) >> 5;
-      const int64_t kblocks = g.kmax >> 5;
-      const int kb_grp = g.kbase[c.grp];
-      uint16_t *st16 = reinterpret_cast<uint16_t *>(stg);
       // The 32 x 32 blocks go in order b = i TN + j; block b + 1's gate / up
       // values are requested before block b is computed and stored, so their
       // latency hides behind that work (the loads would otherwise wait for
@@ -816,6 +713,11 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs g, char *smem, TileCoo
         const int pr = c.prow0 + c.m0 + wm * WM + i * 32 + (lane & 31);
         const int col0 = c.n0 + wn * WN + j * 32;
         return (int64_t(pr >> 4) * gu_blocks + (col0 >> 5) * 2) * 512 + (pr & 15) * 32;
+      };
+      auto act_index = [&](int i, int j) {  // blocked [padded rows][F]
+        const int pr = c.prow0 + c.m0 + wm * WM + i * 32 + (lane & 31);
+        return (int64_t(pr >> 4) * (F >> 5) + ((c.n0 + wn * WN + j * 32) >> 5)) * 512 +
+               (pr & 15) * 32;
       };
       // 16-byte loads (lane l: columns 16 q + 0..7, lane l + 32: 16 q + 8..15),
       // then half-wave swaps give each lane its accumulator columns
@@ -846,13 +748,10 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs g, char *smem, TileCoo
         const int i = b / TN, j = b % TN;
         if (b + 1 < TM * TN) load_block((b + 1) / TN, (b + 1) % TN, gnxt, unxt);
         if (block_ok(i, j)) {
-          const int rr = c.m0 + wm * WM + i * 32;  // first row of the piece in its group
           const bool row_ok = i * 32 + (lane & 31) < rows_w;
-          const int64_t kb = (kb_grp + rr) >> 5;
-          const int col0 = c.n0 + wn * WN + j * 32;  // first activation column f
-          const int64_t gblk = dgu_index(i, j);
+          const int64_t gblk = dgu_index(i, j), ablk = act_index(i, j);
           // two column groups gq = 2 q, 2 q + 1 at a time (columns
-          // 8 gq + 4 h + e of the 32-block; rows past the group's end 0)
+          // 8 gq + 4 h + e of the 32-block)
           uint16_t *dgu = g.C;
 #pragma unroll
           for (int q = 0; q < 2; ++q) {
@@ -862,30 +761,17 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs g, char *smem, TileCoo
               const uint2 gw = gcur[2 * q + s], uw = ucur[2 * q + s];
 #pragma unroll
               for (int e = 0; e < 4; ++e) {
-                dg[s][e] = du[s][e] = av[s][e] = 0.0f;
-                if (row_ok) {
-                  const uint32_t gbits = (e < 2 ? gw.x : gw.y) >> (16 * (e & 1));
-                  const uint32_t ubits = (e < 2 ? uw.x : uw.y) >> (16 * (e & 1));
-                  const float gv = __uint_as_float(gbits << 16), uv = __uint_as_float(ubits << 16);
-                  const float sg = __builtin_amdgcn_rcpf(1.0f + __expf(-gv));
-                  const float da = acc[i][j][4 * (2 * q + s) + e];
-                  dg[s][e] = da * uv * (sg * (1.0f + gv * (1.0f - sg)));
-                  du[s][e] = da * (gv * sg);
-                  av[s][e] = gv * sg * uv;
-                }
+                const uint32_t gbits = (e < 2 ? gw.x : gw.y) >> (16 * (e & 1));
+                const uint32_t ubits = (e < 2 ? uw.x : uw.y) >> (16 * (e & 1));
+                const float gv = __uint_as_float(gbits << 16), uv = __uint_as_float(ubits << 16);
+                const float sg = __builtin_amdgcn_rcpf(1.0f + __expf(-gv));
+                const float da = acc[i][j][4 * (2 * q + s) + e];
+                dg[s][e] = da * uv * (sg * (1.0f + gv * (1.0f - sg)));
+                du[s][e] = da * (gv * sg);
+                av[s][e] = gv * sg * uv;
               }
             }
-            // transposed staging: output o at o * 1024 elements, [column][row]
-#pragma unroll
-            for (int s = 0; s < 2; ++s)
-#pragma unroll
-              for (int e = 0; e < 4; ++e) {
-                const int n = (8 * (2 * q + s) + 4 * h + e) * 32 + (lane & 31);
-                st16[n] = f32_to_bf16(dg[s][e]);
-                st16[1024 + n] = f32_to_bf16(du[s][e]);
-                st16[2048 + n] = f32_to_bf16(av[s][e]);
-              }
-            // [d g | d u] blocked, as 16-byte runs after the half-wave swaps
+            // 16-byte runs after the half-wave swaps
             // (lane l: columns 16 q + 0..7, lane l + 32: 16 q + 8..15)
             uint32_t a0 = pack2(dg[0][0], dg[0][1]), a1 = pack2(dg[0][2], dg[0][3]);
             uint32_t a2 = pack2(dg[1][0], dg[1][1]), a3 = pack2(dg[1][2], dg[1][3]);
@@ -893,35 +779,19 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs g, char *smem, TileCoo
             uint32_t b2 = pack2(du[1][0], du[1][1]), b3 = pack2(du[1][2], du[1][3]);
             swap_halves(a0, a2);
             swap_halves(a1, a3);
+            uint32_t v0 = pack2(av[0][0], av[0][1]), v1 = pack2(av[0][2], av[0][3]);
+            uint32_t v2 = pack2(av[1][0], av[1][1]), v3 = pack2(av[1][2], av[1][3]);
             swap_halves(b0, b2);
             swap_halves(b1, b3);
+            swap_halves(v0, v2);
+            swap_halves(v1, v3);
             if (row_ok) {
+              *reinterpret_cast<uint4 *>(g.act + ablk + 16 * q + 8 * h) =
+                  make_uint4(v0, v1, v2, v3);
               *reinterpret_cast<uint4 *>(dgu + gblk + 16 * q + 8 * h) = make_uint4(a0, a1, a2, a3);
               *reinterpret_cast<uint4 *>(dgu + gblk + 512 + 16 * q + 8 * h) =
                   make_uint4(b0, b1, b2, b3);
             }
-          }
-          // d gate rows 64 (f / 32) + 0..31 and d up rows + 32 of [2F][kmax];
-          // act rows f of [F][kmax]; 16 rows per 1 KB block. Non-temporal
-          // stores: these blocks are read only by the next launch, and kept
-          // out of the L2 they leave the operands of this GEMM there (0.5-1.2%
-          // faster backward; the same for the blocked [d g | d u] above,
-          // which the dX GEMM reads soon after, was 1-3% slower).
-          const int64_t ngate = 2 * col0;  // = 64 * (col0 / 32)
-#pragma unroll
-          for (int bb = 0; bb < 2; ++bb) {
-            const i32x4 vg = *reinterpret_cast<const i32x4 *>(stg + bb * 1024 + lane * 16);
-            const i32x4 vu = *reinterpret_cast<const i32x4 *>(stg + 2048 + bb * 1024 + lane * 16);
-            const i32x4 va = *reinterpret_cast<const i32x4 *>(stg + 4096 + bb * 1024 + lane * 16);
-            __builtin_nontemporal_store(
-                vg, reinterpret_cast<i32x4 *>(g.dgu_t + (((ngate >> 4) + bb) * kblocks + kb) * 512 +
-                                              lane * 8));
-            __builtin_nontemporal_store(
-                vu, reinterpret_cast<i32x4 *>(
-                        g.dgu_t + ((((ngate + 32) >> 4) + bb) * kblocks + kb) * 512 + lane * 8));
-            __builtin_nontemporal_store(
-                va, reinterpret_cast<i32x4 *>(g.act_t + (((col0 >> 4) + bb) * kblocks + kb) * 512 +
-                                              lane * 8));
           }
         }
         if (b + 1 < TM * TN) {
@@ -933,62 +803,8 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs g, char *smem, TileCoo
         }
       }
     } else {
-      // fp32 weight gradient of expert c.e (problem c.p): C[m][n], rows
-      // m < M, written as 16-byte runs of 4 columns. Gate/up problem: column
-      // n = 64 q + cc is gate column 32 q + cc (cc < 32) or up column
-      // 32 q + cc - 32.
-      auto wgrad_epilogue = [&]() {
-        const bool second = c.p == 2;
-        float *C = second ? g.wp[1].C : g.wp[0].C;
-        float *C2 = g.wp[0].C2;
-        const bool gate_up = !second && g.wp[0].gate_up;
-        const int64_t es = second ? g.wp[1].expert_stride : g.wp[0].expert_stride;
-        // The fp32 gradients leave as whole 128-byte row pieces: each 32 x 32
-        // block is written to the wave's staging area (rows RSF bytes apart,
-        // so the 32 rows of a write spread over the banks) and read back so
-        // that store k covers rows 8k .. 8k+7 of the block, lane l row
-        // 8k + l / 8 and columns 4 (l % 8) .. 4 (l % 8) + 3. (Stored straight
-        // from the accumulators, every store instruction wrote 32-byte pieces
-        // of 32 rows, and the many short tiles of the small experts were
-        // bound by those partial-line writes.) The stores are non-temporal:
-        // nothing in the call reads the gradients back.
-        constexpr int RSF = 32 * 4 + 16;
-        static_assert(32 * RSF <= STAGING, "staging");
-        const int ld = gate_up ? (c.N >> 1) : c.N;  // fp32 elements per gradient row
-        const int rr = lane >> 3, rc = (lane & 7) * 4;  // read-back row / column of the lane
-#pragma unroll
-        for (int i = 0; i < TM; ++i) {
-          if (i * 32 >= rows_w) break;
-          const int m0 = c.m0 + wm * WM + i * 32;  // first gradient row of the block
-#pragma unroll
-          for (int j = 0; j < TN; ++j) {
-            const int col0 = c.n0 + wn * WN + j * 32;
-            if (col0 >= c.N) continue;
-            // gate / up columns are interleaved per 32 in the tile: the block
-            // belongs to one of the two gradients, at column 32 (col0 / 64)
-            float *base;
-            if (gate_up)
-              base = ((col0 & 32) ? C2 : C) + int64_t(c.e) * es + 32 * (col0 >> 6);
-            else
-              base = C + int64_t(c.e) * es + col0;
-#pragma unroll
-            for (int gq = 0; gq < 4; ++gq)
-              *reinterpret_cast<f32x4 *>(stg + (lane & 31) * RSF + (8 * gq + 4 * h) * 4) =
-                  f32x4{acc[i][j][4 * gq], acc[i][j][4 * gq + 1], acc[i][j][4 * gq + 2],
-                        acc[i][j][4 * gq + 3]};
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-              const int r = 8 * k + rr;
-              const f32x4 v = *reinterpret_cast<const f32x4 *>(stg + r * RSF + rc * 4);
-              if (i * 32 + r < rows_w)
-                __builtin_nontemporal_store(
-                    v, reinterpret_cast<f32x4 *>(base + int64_t(m0 + r) * ld + rc));
-            }
-          }
-        }
-      };
       // row-major C: 32 rows x WN columns per piece, rows RS bytes apart
-      auto rowmajor_epilogue = [&]() {
+      {
         static_assert(!kCBlocked, "blocked C: other epilogues");
         // row stride padded by 16 bytes: the 32 rows of a piece then fall
         // into different banks
@@ -1017,14 +833,6 @@ __device__ __forceinline__ void gemm_tiles(const GemmArgs g, char *smem, TileCoo
                   *reinterpret_cast<const i32x4 *>(stg + row * RS + ch * 16);
           }
         }
-      };
-      if constexpr (kMulti) {
-        if (c.p != 0)
-          wgrad_epilogue();
-        else
-          rowmajor_epilogue();
-      } else {
-        rowmajor_epilogue();
       }
     }
     sched.done(c, more);
@@ -1046,8 +854,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N)
 __attribute__((amdgpu_waves_per_eu(WAVES_M * WAVES_N / 4, WAVES_M * WAVES_N / 4)))
 void gemm256_kernel(GemmArgs g) {
   __shared__ __attribute__((aligned(1024))) char smem[ring_bytes<BN>()];
-  __shared__ int32_t s_next;  // multi-problem launch: the next tile from the counter
-  LaunchSched<256, BN, kEpi == kEpiBwdMulti> sched(g, &s_next);
+  LaunchSched<256, BN> sched(g);
   TileCoord t;
   if (!sched.first(t)) return;
   gemm_tiles<BN, WAVES_M, WAVES_N, kEpi, kABlocked, kCBlocked>(g, smem, t, sched);

@@ -190,6 +190,7 @@ static_assert(kClaimWave >= kWavesM * kWavesN / 2 && kClaimWave < kWavesM * kWav
 template <int kPhase, int BN1, int BN2>
 struct FusedSched {
   static constexpr int BN = kPhase == 0 ? BN1 : BN2;
+  static constexpr bool kOpaqueLane = false;
   static constexpr bool kCoherentC = kPhase == 0;  // the activations
   const int4 *tiles;
   const int32_t *groups;
@@ -293,18 +294,14 @@ struct FusedSched {
                                        TileCoord &c) const {
     int nt, mt;
     locate(it, nt, mt);
-    c.grp = te.x;
     c.e = e;
     c.row0 = row0;
     c.prow0 = te.z;
     c.m0 = te.y * kTileM;
     c.rows_valid = min(kTileM, n - c.m0);
-    c.N = N;
     c.n0 = nt * BN;
     c.cols_valid = min(BN, N - c.n0);
-    c.k0 = 0;
     c.nk = nk;
-    c.p = 0;
     c.mt = mt;
   }
   // thread 0: wait until every phase-0 tile of m-tile mt has stored its

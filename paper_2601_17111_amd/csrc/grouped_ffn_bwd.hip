@@ -2,9 +2,10 @@
 // input gradients of the range's rows and per-expert weight gradients with
 // the gradient return of spilled chunks (Sec. 1 and Sec. 4: LLEP stays exact
 // in training, the spilled chunks' weight gradients go back to the expert's
-// native device and are added there). The GEMMs are gemm.h's kernel with its
-// backward epilogues.
+// native device and are added there). The GEMMs are gemm.h's kernel and
+// wgrad.h's weight-gradient tiles.
 #include "gemm.h"
+#include "wgrad.h"
 
 namespace llep {
 
@@ -16,41 +17,35 @@ namespace llep {
 //      forward kept them
 //   2. d act = d out Wd^T; epilogue: d g, d u and act = silu(g) u
 //   3. dX = [d g | d u] [Wg | Wu]^T               (x_perm rows)
-//   4. weight gradients, in fp32 per expert: the rows of an expert's groups
-//      are laid end to end in gradient-return order (the group on the
-//      expert's native device first, then the other devices in increasing
-//      order; each group padded with zero rows to a multiple of 32), and
-//      dWg | dWu = X^T [d g | d u], dWd = act^T d out contract over that
-//      segment, so an expert's gradient sums its native partial and then the
-//      returned partials, in a fixed order.
+//   4. weight gradients, in fp32 per expert: dWg | dWu = X^T [d g | d u] and
+//      dWd = act^T d out, contracted over the rows of the expert's groups in
+//      gradient-return order (the group on the expert's native device first,
+//      then the other devices in increasing order), so an expert's gradient
+//      sums its native partial and then the returned partials, in a fixed
+//      order.
 // ---------------------------------------------------------------------------
 
 struct BwdLayout {
-  size_t tiles_off, wge_off, kbase_off, chunk_off;
-  size_t gu_off, dgu_off, xt_off, dot_off, actt_off, dgut_off, total;
-  int64_t max_groups, max_mtiles, prow_max, kmax;
+  size_t tiles_off, wge_off, wgg_off, gu_off, dgu_off, act_off, total;
+  int64_t max_groups, max_mtiles, prow_max;
 };
 
 static size_t round256(size_t v) { return (v + 255) / 256 * 256; }
 
-static BwdLayout bwd_layout(int64_t R, int32_t E, int32_t P, int32_t D, int32_t F) {
+static BwdLayout bwd_layout(int64_t R, int32_t E, int32_t P, int32_t F) {
   BwdLayout L;
   L.max_groups = 2 * int64_t(E) + P;
   L.max_mtiles = R / kTileM + L.max_groups + 1;
-  L.prow_max = R + 16 * L.max_groups;
-  L.kmax = (R + 32 * L.max_groups + 31) / 32 * 32;
-  size_t o = 256;  // counters: n_mtiles, n_wg, k-slices in use, work counter, long n_wg,
-                   // copy counter
+  // a weight-gradient slice reads two 16-row blocks, also where its group
+  // ends in the first: one block more than the padded rows
+  L.prow_max = R + 16 * L.max_groups + 16;
+  size_t o = 256;  // counters: n_mtiles, n_wg, work counter, long n_wg
   L.tiles_off = o;  o = round256(o + size_t(L.max_mtiles) * 16);
   L.wge_off = o;    o = round256(o + size_t(E) * 16);
-  L.kbase_off = o;  o = round256(o + size_t(L.max_groups) * 4);
-  L.chunk_off = o;  o = round256(o + size_t(L.kmax / 32) * 4);
+  L.wgg_off = o;    o = round256(o + size_t(L.max_groups) * 16);
   L.gu_off = o;     o = round256(o + size_t(R) * 2 * F * 2);  // by x_perm row
   L.dgu_off = o;    o = round256(o + size_t(L.prow_max) * 2 * F * 2);
-  L.xt_off = o;     o = round256(o + size_t(D) * L.kmax * 2);
-  L.dot_off = o;    o = round256(o + size_t(D) * L.kmax * 2);
-  L.actt_off = o;   o = round256(o + size_t(F) * L.kmax * 2);
-  L.dgut_off = o;   o = round256(o + size_t(2 * F) * L.kmax * 2);
+  L.act_off = o;    o = round256(o + size_t(L.prow_max) * F * 2);
   L.total = o;
   return L;
 }
@@ -62,215 +57,213 @@ static size_t f32_bwd_bytes(int64_t R, int32_t F) {
 }
 
 bool ffn_backward_rows_ok(int64_t R, int32_t E, int32_t P) {
-  // a DMA lane's byte offset reaches 16 blocks of kmax / 32 KB each
-  return bwd_layout(R, E, P, 64, 64).kmax * 512 <= int64_t(INT32_MAX);
+  // the documented limit of the call: 512 bytes for each of the rows, the
+  // groups padded to 32, in 31 bits
+  const int64_t max_groups = 2 * int64_t(E) + P;
+  return (R + 32 * max_groups + 31) / 32 * 32 * 512 <= int64_t(INT32_MAX);
 }
 
 size_t ffn_backward_workspace_bytes(int64_t R, int32_t E, int32_t P, int32_t D, int32_t F,
                                     llep_dtype dtype) {
   if (dtype == LLEP_F32) return f32_bwd_bytes(R, F);
-  return bwd_layout(R, E, P, D, F).total;
+  return bwd_layout(R, E, P, F).total;
 }
 
-// One workgroup. For the groups [lo, hi) of the range: each group's first
-// weight-gradient row (kbase[group], a multiple of 32) in gradient-return
-// order, the owner group of every 32-row chunk, and the
-// experts present with their segment (first 32-row slice, slices), longest
-// segment first (ties: lower expert id), and how many of them have at least
-// long_slices slices (those tiles are handed out before the input-gradient
-// tiles, the shorter ones after them). Zeroes the work counters of the
-// multi-problem launch and of the d act launch's copies.
-__global__ __launch_bounds__(1024) void wgrad_table_kernel(
-    const int32_t *__restrict__ groups, const int32_t *__restrict__ group_begin, int32_t device,
-    int32_t P, int32_t E, int32_t M, int32_t *__restrict__ kbase,
-    int32_t *__restrict__ chunk_group, int4 *__restrict__ wg_experts, int32_t *__restrict__ n_wg,
-    int32_t long_slices, int32_t *__restrict__ n_wg_long, int32_t *__restrict__ kslices,
-    int32_t *__restrict__ queue, int32_t *__restrict__ copy_counter) {
-  __shared__ int32_t se[kMaxChunks], skey[kMaxChunks], ssl[kMaxChunks], skb[kMaxChunks];
-  __shared__ int32_t esl[LLEP_MAX_EXPERTS];
+// One workgroup. For the groups [lo, hi) of the range, sorted by expert and
+// within an expert in gradient-return order: their first x_perm row, first
+// 16-row block of padded rows, and rows; and the experts present with their
+// first group and 32-row slices (each group's rounded up), most slices first
+// (ties: lower expert id), and how many of them have at least long_slices
+// slices (those tiles are handed out before the input-gradient tiles, the
+// shorter ones after them). Zeroes the work counter of the multi-problem
+// launch. Bound by latency: one scan over the groups (padded rows) and one
+// over the experts (groups), and for an expert with several groups a count
+// over the groups (qwen3-30b-a3b, 8192 tokens: 42 us with counts over all
+// groups for every group).
+constexpr int kTableThreads = 1024;
+
+// exclusive sum over the workgroup's threads; *total: the sum
+__device__ __forceinline__ int32_t block_scan(int32_t v, int32_t *wsum, int32_t *total) {
+  const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+  int32_t incl = v;
+  for (int off = 1; off < kWave; off <<= 1) {
+    const int32_t u = __shfl_up(incl, off);
+    if (lane >= off) incl += u;
+  }
+  if (lane == kWave - 1) wsum[wave] = incl;
+  __syncthreads();
+  int32_t before = 0, sum = 0;
+#pragma unroll
+  for (int w = 0; w < kTableThreads / kWave; ++w) {
+    const int32_t x = wsum[w];
+    before += w < wave ? x : 0;
+    sum += x;
+  }
+  *total = sum;
+  __syncthreads();
+  return before + incl - v;
+}
+
+__global__ __launch_bounds__(kTableThreads) void wgrad_table_kernel(
+    const int32_t *__restrict__ groups, const int32_t *__restrict__ group_begin, int32_t cap,
+    int32_t device, int32_t P, int32_t E, int32_t M, int4 *__restrict__ wg_groups,
+    int4 *__restrict__ wg_experts, int32_t *__restrict__ n_wg, int32_t long_slices,
+    int32_t *__restrict__ n_wg_long, int32_t *__restrict__ queue) {
+  constexpr int kPer = 2;  // adjacent groups per thread
+  static_assert(kPer * kTableThreads >= kMaxChunks && LLEP_MAX_EXPERTS <= kTableThreads, "threads");
+  __shared__ int32_t ge[kMaxChunks];                 // (expert << 1) | native
+  __shared__ int32_t count[LLEP_MAX_EXPERTS], slices[LLEP_MAX_EXPERTS];
+  __shared__ int32_t wsum[kTableThreads / kWave];
+  __shared__ int32_t n_all, n_long;
   const int tid = threadIdx.x;
   const int lo = device < 0 ? group_begin[0] : group_begin[device];
-  const int hi = device < 0 ? group_begin[P] : group_begin[device + 1];
-  const int G = min(hi - lo, kMaxChunks);
-  for (int i = tid; i < G; i += blockDim.x) {
-    const int32_t *gr = groups + 4 * (lo + i);
-    const int d = gr[0], e = gr[1], n = gr[3];
-    se[i] = e;
-    skey[i] = d == e / M ? -1 : d;  // native device first
-    ssl[i] = (n + 31) / 32;
+  const int hi = min(cap, device < 0 ? group_begin[P] : group_begin[device + 1]);
+  const int G = min(max(hi - lo, 0), kMaxChunks);
+  int e[kPer], nat[kPer], row[kPer], n[kPer];
+  int32_t pad = 0;
+#pragma unroll
+  for (int j = 0; j < kPer; ++j) {
+    const int i = kPer * tid + j;
+    const int32_t *p = groups + 4 * min(lo + i, cap - 1);
+    e[j] = p[1];
+    nat[j] = p[0] == e[j] / M;
+    row[j] = p[2];
+    n[j] = i < G ? p[3] : 0;
+    pad += (n[j] + 15) / 16;
+  }
+  for (int x = tid; x < E; x += kTableThreads) count[x] = slices[x] = 0;
+  if (tid == 0) n_all = n_long = 0;
+  int32_t total;
+  int32_t block = block_scan(pad, wsum, &total);  // (its barriers order the clearing)
+#pragma unroll
+  for (int j = 0; j < kPer; ++j) {
+    const int i = kPer * tid + j;
+    if (i >= G) continue;
+    ge[i] = (e[j] << 1) | nat[j];
+    atomicAdd(&count[e[j]], 1);
+    atomicAdd(&slices[e[j]], (n[j] + 31) / 32);
   }
   __syncthreads();
-  // (the loops over groups and experts below are unrolled so that their
-  // LDS reads, which do not depend on one another, are in flight together)
-  for (int i = tid; i < G; i += blockDim.x) {
-    int32_t kb = 0;
+  const int32_t own = tid < E ? count[tid] : 0, sl = tid < E ? slices[tid] : 0;
+  const int32_t first = block_scan(own, wsum, &total);
+  if (tid < E) {
+    // position among the experts by slices
+    if (sl > 0) {
+      int32_t at = 0;
 #pragma unroll 8
-    for (int j = 0; j < G; ++j)
-      if (se[j] < se[i] || (se[j] == se[i] && skey[j] < skey[i])) kb += ssl[j];
-    kbase[lo + i] = kb * 32;
-    skb[i] = kb;
-  }
-  for (int e = tid; e < E; e += blockDim.x) {
-    int32_t sl = 0;
-#pragma unroll 8
-    for (int j = 0; j < G; ++j) sl += se[j] == e ? ssl[j] : 0;
-    esl[e] = sl;
+      for (int f = 0; f < E; ++f) at += slices[f] > sl || (slices[f] == sl && f < tid);
+      wg_experts[at] = make_int4(tid, first, sl, 0);
+      atomicAdd(&n_all, 1);
+      if (sl >= long_slices) atomicAdd(&n_long, 1);
+    }
+    count[tid] = (first << 1) | (own > 1);  // (read by its own thread above)
   }
   __syncthreads();
-  // owner group of every 32-row slice: one wave per group, its lanes
-  // striding over the group's slices
-  for (int i = tid / kWave; i < G; i += blockDim.x / kWave)
-    for (int c = skb[i] + tid % kWave; c < skb[i] + ssl[i]; c += kWave) chunk_group[c] = lo + i;
-  for (int e = tid; e < E; e += blockDim.x) {
-    const int32_t sl = esl[e];
-    if (sl == 0) continue;
-    int32_t idx = 0, start = 0;
-#pragma unroll 8
-    for (int f = 0; f < E; ++f) idx += esl[f] > sl || (esl[f] == sl && f < e);
-#pragma unroll 8
-    for (int j = 0; j < G; ++j) start += se[j] < e ? ssl[j] : 0;
-    wg_experts[idx] = make_int4(e, start, sl, 0);
+#pragma unroll
+  for (int j = 0; j < kPer; ++j) {
+    const int i = kPer * tid + j;
+    if (i >= G) continue;
+    const int32_t c = count[e[j]];
+    int32_t at = c >> 1;
+    if ((c & 1) && !nat[j]) {
+      // the native group, then the groups of smaller devices (the table is
+      // device-major, so they come before this one)
+#pragma unroll 4
+      for (int g = 0; g < G; ++g) at += ge[g] >> 1 == e[j] && (g < i || (ge[g] & 1));
+    }
+    wg_groups[at] = make_int4(row[j], block, n[j], 0);
+    block += (n[j] + 15) / 16;
   }
-  // counts over the experts and groups: one wave, lanes striding, then a
-  // wave sum
-  if (tid < kWave) {
-    int32_t n = 0, nl = 0, tot = 0;
-    for (int e = tid; e < E; e += kWave) {
-      n += esl[e] > 0;
-      nl += esl[e] > 0 && esl[e] >= long_slices;
-    }
-    for (int j = tid; j < G; j += kWave) tot += ssl[j];
-    for (int off = kWave / 2; off > 0; off >>= 1) {
-      n += __shfl_xor(n, off);
-      nl += __shfl_xor(nl, off);
-      tot += __shfl_xor(tot, off);
-    }
-    if (tid == 0) {
-      *n_wg = n;
-      *n_wg_long = nl;
-      *kslices = tot;
-      *queue = 0;
-      *copy_counter = 0;
-    }
+  if (tid == 0) {
+    *n_wg = n_all;
+    *n_wg_long = n_long;
+    *queue = 0;
   }
 }
 
-// The other weight-gradient operands: C columns of the range's rows
-// (row-major by x_perm row, ld elements) copied into the weight-gradient
-// layout, blocks of 16 columns x 32 rows over [C][kmax], row kbase[g] + r of
-// the layout = row r of group g (zero for the padding r >= n_g). Item i of a
-// source is its 32-row slice c = i / (C / 64) and its 64-column group
-// i % (C / 64); the two sources (X, d out) follow one another.
-struct WgradCopy {
-  const uint16_t *src[2];
-  uint16_t *dst[2];
-  int64_t ld;
-  int32_t C;  // a multiple of 64
-  int64_t kmax;
-  const int32_t *groups, *kbase, *chunk_group, *kslices;
-  int32_t *counter;  // items taken; zeroed by the table kernel
+// Step 3: the weight-gradient tiles (wgrad.h) and the input-gradient tiles
+// (gemm.h) from one work counter, longest first, so that the last ones to
+// start are short and the workgroups finish together: the weight-gradient
+// tiles of the experts whose contraction is at least as long as an
+// input-gradient tile's, then the input-gradient tiles, then the other
+// weight-gradient tiles. A workgroup's first tile is its slot (each XCD a
+// contiguous block of the order); it asks for the next one while it works.
+struct BwdQueue {
+  int n_long, n_wgt, n_main, n_mt, n_nt, per0, per1, G;
+  int32_t *counter, *s_next;
+  int u;  // the tile taken last
+
+  __device__ __forceinline__ bool is_wg(int v) const {
+    return v < n_long || (v >= n_long + n_main && v < n_wgt + n_main);
+  }
+  __device__ __forceinline__ void ask() const {
+    if (threadIdx.x == 0) *s_next = atomicAdd(counter, 1) + G;
+  }
+  __device__ __forceinline__ void take() { u = __builtin_amdgcn_readfirstlane(*s_next); }
 };
 
-constexpr int kCopyBatch = 8;             // items per counter claim
-constexpr int kCopyTileBytes = 64 * 32 * 2;  // LDS staging tile of one wave
-
-// One wavefront copies items taken kCopyBatch at a time from w.counter until
-// none is left, with no barrier: each wave stages through its own LDS tile
-// (`tile`, kCopyTileBytes) of 64 columns x 32 rows, column-major, the four
-// 8-row chunks of column col in slots chunk ^ ((col / 8) % 4) so that a
-// write instruction spreads over the banks. The loads of a batch are all
-// issued before its first item is staged.
-__device__ __forceinline__ void wgrad_copy_items(const WgradCopy &w, uint16_t *tile) {
-  const int lane = threadIdx.x & 63;
-  const int cgroups = w.C / 64;
-  const int per_src = __builtin_amdgcn_readfirstlane(*w.kslices) * cgroups;
-  const int n_items = 2 * per_src;
-  // load layout: lane l holds row 8 q + l / 8 of the slice, columns
-  // 8 (l % 8) .. + 7 of the item's 64 (each load instruction covers 8 whole
-  // rows of 128 bytes)
-  const int a = lane & 7, b = lane >> 3;
-  const bool odd = b & 1;
-  for (;;) {
-    int b0 = 0;
-    if (lane == 0) b0 = atomicAdd(w.counter, kCopyBatch);
-    b0 = __builtin_amdgcn_readfirstlane(b0);
-    if (b0 >= n_items) break;
-    i32x4 v[kCopyBatch][4];
-#pragma unroll
-    for (int j = 0; j < kCopyBatch; ++j) {
-      const int i = min(b0 + j, n_items - 1);  // past the end: the last item again (not stored)
-      const int s = i >= per_src, rem = i - s * per_src;
-      const int c = rem / cgroups, cc = rem - c * cgroups;
-      const int gi = w.chunk_group[c];
-      const int n = w.groups[4 * gi + 3];
-      const int r0 = c * 32 - w.kbase[gi];
-      const uint16_t *src = w.src[s] + int64_t(w.groups[4 * gi + 2]) * w.ld + cc * 64 + a * 8;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int row = r0 + 8 * q + b;
-        v[j][q] = i32x4{0, 0, 0, 0};
-        if (row < n) v[j][q] = *reinterpret_cast<const i32x4 *>(src + int64_t(row) * w.ld);
-      }
-    }
-#pragma unroll
-    for (int j = 0; j < kCopyBatch; ++j) {
-      const int i = b0 + j;
-      if (i >= n_items) break;
-      const int s = i >= per_src, rem = i - s * per_src;
-      const int c = rem / cgroups, cc = rem - c * cgroups;
-      // the previous item's reads of the tile are done before it is rewritten
-      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-      // Lanes l and l ^ 8 hold rows r and r ^ 1 of the same columns: each
-      // writes one 32-bit word of two rows, the even-row lane for the even
-      // column of a pair, the odd-row lane for the odd one.
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const uint32_t mine = uint32_t(v[j][q][e]);
-          const uint32_t other = uint32_t(__shfl_xor(int(mine), 8));
-          const uint32_t word = odd ? ((other >> 16) | (mine & 0xffff0000u))
-                                    : ((mine & 0xffffu) | (other << 16));
-          const int col = 8 * a + 2 * e + int(odd);
-          *reinterpret_cast<uint32_t *>(tile + col * 32 + ((q ^ (a & 3)) << 3) + (b & 6)) = word;
-        }
-      }
-      // the tile is written before any lane reads it back
-      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-      // block bb: columns 16 bb .. 16 bb + 15; lane l column l / 4, rows
-      // 8 (l % 4) .. + 7
-      uint16_t *dst = w.dst[s] + int64_t(c) * 512 + (lane >> 2) * 32 + (lane & 3) * 8;
-#pragma unroll
-      for (int bb = 0; bb < 4; ++bb) {
-        const int col = bb * 16 + (lane >> 2);
-        *reinterpret_cast<i32x4 *>(dst + int64_t(cc * 4 + bb) * (w.kmax / 32) * 512) =
-            *reinterpret_cast<const i32x4 *>(tile + col * 32 + (((lane & 3) ^ ((col >> 3) & 3)) << 3));
-      }
-    }
+struct WgSched {
+  const WgArgs &w;
+  BwdQueue &q;
+  __device__ __forceinline__ void decode(WgTile &t) const {
+    wg_decode(w, q.u < q.n_long ? q.u : q.u - q.n_main, q.per0, q.per1, t);
   }
-}
+  __device__ __forceinline__ void request() const { q.ask(); }
+  __device__ __forceinline__ bool next(WgTile &t) {
+    q.take();
+    if (!q.is_wg(q.u)) return false;
+    decode(t);
+    return true;
+  }
+};
 
-// Step 2 of the backward (d act GEMM with the SwiGLU backward epilogue) and
-// the copies of X and d out into the weight-gradient layout in one launch:
-// the GEMM deals its tiles in rounds, so the workgroups without a tile in the
-// last, partly filled round start on the copies while the others finish
-// their tiles, and everyone takes copy items once its tiles are done.
-template <int BN, int WAVES_M, int WAVES_N>
-__global__ __launch_bounds__(64 * WAVES_M * WAVES_N)
-__attribute__((amdgpu_waves_per_eu(WAVES_M * WAVES_N / 4, WAVES_M * WAVES_N / 4)))
-void dact_kernel(GemmArgs g, WgradCopy w) {
-  static_assert(WAVES_M * WAVES_N * kCopyTileBytes <= ring_bytes<BN>(), "copy tiles fit the ring");
-  __shared__ __attribute__((aligned(1024))) char smem[ring_bytes<BN>()];
+struct DxSched {
+  static constexpr bool kOpaqueLane = true;  // two loops: registers are short
+  static constexpr bool kCoherentC = false;  // C is read only by later launches
+  const GemmArgs &g;
+  BwdQueue &q;
+  __device__ __forceinline__ bool decode(TileCoord &t) const {
+    return decode_tile<256, 192>(g, q.u - q.n_long, q.n_mt, q.n_nt, t);
+  }
+  __device__ __forceinline__ void request() const { q.ask(); }
+  __device__ __forceinline__ bool next(TileCoord &t) {
+    q.take();
+    return !q.is_wg(q.u) && q.u < q.n_wgt + q.n_main && decode(t);
+  }
+  __device__ __forceinline__ void done(const TileCoord &, bool) const {}
+};
+
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void bwd_multi_kernel(GemmArgs g, WgArgs w, int32_t *counter) {
+  __shared__ __attribute__((aligned(1024))) char smem[ring_bytes<192>()];
   __shared__ int32_t s_next;
-  {
-    LaunchSched<256, BN, false> sched(g, &s_next);
-    TileCoord t;
-    if (sched.first(t)) gemm_tiles<BN, WAVES_M, WAVES_N, kEpiSwigluBwd, false, true>(g, smem, t, sched);
+  BwdQueue q;
+  q.n_mt = __builtin_amdgcn_readfirstlane(*g.n_mtiles);
+  q.n_nt = (g.N + 191) / 192;
+  q.n_main = q.n_mt * q.n_nt;
+  q.per0 = ((w.p[0].M + 255) / 256) * ((w.p[0].N + 191) / 192);
+  q.per1 = ((w.p[1].M + 255) / 256) * ((w.p[1].N + 191) / 192);
+  q.n_wgt = __builtin_amdgcn_readfirstlane(*w.n_experts) * (q.per0 + q.per1);
+  q.n_long = __builtin_amdgcn_readfirstlane(*w.n_long) * (q.per0 + q.per1);
+  q.G = gridDim.x;  // a multiple of 8
+  q.counter = counter;
+  q.s_next = &s_next;
+  q.u = (blockIdx.x % 8) * (q.G / 8) + blockIdx.x / 8;
+  while (q.u < q.n_wgt + q.n_main) {
+    if (q.is_wg(q.u)) {
+      WgSched s{w, q};
+      WgTile t;
+      s.decode(t);
+      wgrad_tiles(w, smem, t, s);
+    } else {
+      DxSched s{g, q};
+      TileCoord t;
+      if (!s.decode(t)) break;
+      gemm_tiles<192, kWavesM192, kWavesN192, kEpiPlain, true, false>(g, smem, t, s);
+    }
+    // the last epilogue's staging reads are done before the ring fills again
+    wait_and_sync<63>();
   }
-  // every wave is done with the ring (its last epilogue's staging reads)
-  // before the copies reuse it
-  __syncthreads();
-  wgrad_copy_items(w, reinterpret_cast<uint16_t *>(smem + (threadIdx.x >> 6) * kCopyTileBytes));
 }
 
 // ---------------------------------------------------------------------------
@@ -338,24 +331,18 @@ hipError_t launch_grouped_ffn_backward(const FfnBwdArgs &a, hipStream_t stream) 
     float *dgu = reinterpret_cast<float *>(static_cast<char *>(a.ws) + 256);
     return launch_ffn_f32_backward(a, dgu, dgu + size_t(a.R) * 2 * a.F, stream);
   }
-  const BwdLayout L = bwd_layout(a.R, a.E, a.P, a.D, a.F);
+  const BwdLayout L = bwd_layout(a.R, a.E, a.P, a.F);
   char *ws = static_cast<char *>(a.ws);
   int32_t *n_mtiles = reinterpret_cast<int32_t *>(ws);
   int32_t *n_wg = n_mtiles + 1;
-  int32_t *kslices = n_mtiles + 2;
-  int32_t *queue = n_mtiles + 3;
-  int32_t *n_wg_long = n_mtiles + 4;
-  int32_t *copy_counter = n_mtiles + 5;
+  int32_t *queue = n_mtiles + 2;
+  int32_t *n_wg_long = n_mtiles + 3;
   int4 *tiles = reinterpret_cast<int4 *>(ws + L.tiles_off);
   int4 *wge = reinterpret_cast<int4 *>(ws + L.wge_off);
-  int32_t *kbase = reinterpret_cast<int32_t *>(ws + L.kbase_off);
-  int32_t *chunk = reinterpret_cast<int32_t *>(ws + L.chunk_off);
+  int4 *wgg = reinterpret_cast<int4 *>(ws + L.wgg_off);
   uint16_t *gu = reinterpret_cast<uint16_t *>(ws + L.gu_off);
   uint16_t *dgu = reinterpret_cast<uint16_t *>(ws + L.dgu_off);
-  uint16_t *xt = reinterpret_cast<uint16_t *>(ws + L.xt_off);
-  uint16_t *dot = reinterpret_cast<uint16_t *>(ws + L.dot_off);
-  uint16_t *actt = reinterpret_cast<uint16_t *>(ws + L.actt_off);
-  uint16_t *dgut = reinterpret_cast<uint16_t *>(ws + L.dgut_off);
+  uint16_t *act = reinterpret_cast<uint16_t *>(ws + L.act_off);
   const int grid = (cu_count() + 7) / 8 * 8;
   const int D = a.D, F = a.F;
   hipError_t err;
@@ -367,13 +354,12 @@ hipError_t launch_grouped_ffn_backward(const FfnBwdArgs &a, hipStream_t stream) 
   err = launch_tile_table(a.groups, a.group_begin, 2 * a.E + a.P, a.device, a.P, tiles, n_mtiles,
                           stream);
   if (err != hipSuccess) return err;
-  hipLaunchKernelGGL(wgrad_table_kernel, dim3(1), dim3(1024), 0, stream, a.groups, a.group_begin,
-                     a.device, a.P, a.E, a.E / a.P, kbase, chunk, wge, n_wg, 2 * F / kSK,
-                     n_wg_long, kslices, queue, copy_counter);
+  hipLaunchKernelGGL(wgrad_table_kernel, dim3(1), dim3(kTableThreads), 0, stream, a.groups,
+                     a.group_begin, 2 * a.E + a.P, a.device, a.P, a.E, a.E / a.P, wgg, wge, n_wg,
+                     2 * F / kSK, n_wg_long, queue);
   LLEP_CHECK_LAUNCH();
   constexpr int NT = 64 * kWavesM * kWavesN;
   constexpr int NT192 = 64 * kWavesM192 * kWavesN192;
-  const bool d192 = D % 256 != 0 && D % 192 == 0;
   const bool f192 = F % 256 != 0 && F % 192 == 0;
   // 1. g, u = X [Wg | Wu] (interleaved per 32), row-major by x_perm row,
   // unless the forward saved them
@@ -395,10 +381,8 @@ hipError_t launch_grouped_ffn_backward(const FfnBwdArgs &a, hipStream_t stream) 
                        dim3(grid), dim3(NT), 0, stream, g);
     LLEP_CHECK_LAUNCH();
   }
-  // 2. d act = d out Wd^T; the epilogue writes [d g | d u] blocked (for dX)
-  // and [d g | d u], act transposed into the weight-gradient layout; in the
-  // same launch, the other weight-gradient operands X and d out, with the
-  // rows of each expert laid end to end along k (gradient-return order)
+  // 2. d act = d out Wd^T; the epilogue writes [d g | d u] and act blocked
+  // over padded rows
   GemmArgs g2 = g;
   g2.A = static_cast<const uint16_t *>(a.d_out_perm);
   g2.lda = D;
@@ -410,33 +394,17 @@ hipError_t launch_grouped_ffn_backward(const FfnBwdArgs &a, hipStream_t stream) 
   g2.N = F;
   g2.Kdim = D;
   g2.GU = a.gate_up ? static_cast<const uint16_t *>(a.gate_up) : gu;
-  g2.dgu_t = dgut;
-  g2.act_t = actt;
-  g2.kbase = kbase;
-  g2.kmax = L.kmax;
-  WgradCopy wc = {};
-  wc.src[0] = static_cast<const uint16_t *>(a.x_perm);
-  wc.src[1] = static_cast<const uint16_t *>(a.d_out_perm);
-  wc.dst[0] = xt;
-  wc.dst[1] = dot;
-  wc.ld = D;
-  wc.C = D;
-  wc.kmax = L.kmax;
-  wc.groups = a.groups;
-  wc.kbase = kbase;
-  wc.chunk_group = chunk;
-  wc.kslices = kslices;
-  wc.counter = copy_counter;
+  g2.act = act;
   if (f192)
-    hipLaunchKernelGGL((dact_kernel<192, kWavesM192, kWavesN192>), dim3(grid), dim3(NT192), 0,
-                       stream, g2, wc);
+    hipLaunchKernelGGL((gemm256_kernel<192, kWavesM192, kWavesN192, kEpiSwigluBwd, false, true>),
+                       dim3(grid), dim3(NT192), 0, stream, g2);
   else
-    hipLaunchKernelGGL((dact_kernel<256, kWavesM, kWavesN>), dim3(grid), dim3(NT), 0, stream, g2,
-                       wc);
+    hipLaunchKernelGGL((gemm256_kernel<256, kWavesM, kWavesN, kEpiSwigluBwd, false, true>),
+                       dim3(grid), dim3(NT), 0, stream, g2);
   LLEP_CHECK_LAUNCH();
   // 3. one launch: dX = [d g | d u] [Wg | Wu]^T into the x_perm rows, and
   // the weight gradients X^T [d g | d u] (de-interleaved into dWg, dWu) and
-  // act^T d out, per expert over its k-segment
+  // act^T d out, per expert over its rows
   GemmArgs g3 = g;
   g3.A = dgu;
   g3.lda = 2 * F;
@@ -448,17 +416,14 @@ hipError_t launch_grouped_ffn_backward(const FfnBwdArgs &a, hipStream_t stream) 
   g3.ldc = D;
   g3.N = D;
   g3.Kdim = 2 * F;
-  const int64_t wblk = (L.kmax / 32) * 1024;
-  g3.wp[0] = WgProblem{xt, dgut, wblk, a.dw_gate, a.dw_up, int64_t(D) * F, D, 2 * F, 1};
-  g3.wp[1] = WgProblem{actt, dot, wblk, a.dw_down, nullptr, int64_t(F) * D, F, D, 0};
-  g3.wg_experts = wge;
-  g3.n_wg = n_wg;
-  g3.n_wg_long = n_wg_long;
-  g3.queue = queue;
-  // 256 x 192 tiles: the 256 x 256 ring fills the LDS and leaves no room for
-  // the work counter's broadcast slot
-  hipLaunchKernelGGL((gemm256_kernel<192, kWavesM192, kWavesN192, kEpiBwdMulti, true, false>),
-                     dim3(grid), dim3(NT192), 0, stream, g3);
+  WgArgs w = {};
+  w.p[0] = WgProblem{static_cast<const uint16_t *>(a.x_perm), dgu, a.dw_gate, a.dw_up, D, 2 * F};
+  w.p[1] = WgProblem{static_cast<const uint16_t *>(a.d_out_perm), act, a.dw_down, nullptr, D, F};
+  w.experts = wge;
+  w.groups = wgg;
+  w.n_experts = n_wg;
+  w.n_long = n_wg_long;
+  hipLaunchKernelGGL(bwd_multi_kernel, dim3(grid), dim3(NT192), 0, stream, g3, w, queue);
   LLEP_CHECK_LAUNCH();
 #undef LLEP_CHECK_LAUNCH
   return hipSuccess;
