@@ -50,8 +50,8 @@ size_t ffn_workspace_bytes(int64_t R, int32_t E, int32_t P, int32_t F, llep_dtyp
 // rows of each group of the range. Padded rows: the groups' rows laid end to
 // end with each group rounded up to a multiple of 16 (the row blocks of the
 // activation matrix). Also zeroes the single launch's counters (seq [2][8]
-// and done [tiles]) when given: a kernel, not a memset, so the call can be
-// captured in a graph.
+// and done [tiles]): a kernel, not a memset, so the call can be captured in a
+// graph.
 // ---------------------------------------------------------------------------
 
 // Thread t holds the entries 5t .. 5t+4 of the group table (up to its
@@ -116,17 +116,8 @@ __global__ __launch_bounds__(kTileTableThreads) void tile_table_kernel(
     pbase += pr[j];
   }
   if (tid == 0) *n_tiles = total;
-  if (seq != nullptr && tid < 16) seq[tid] = 0;
-  if (done != nullptr)
-    for (int i = tid; i < total; i += kTileTableThreads) done[i] = 0;
-}
-
-hipError_t launch_tile_table(const int32_t *groups, const int32_t *group_begin, int32_t cap,
-                             int32_t device, int32_t P, int4 *tiles, int32_t *n_tiles,
-                             hipStream_t stream) {
-  hipLaunchKernelGGL(tile_table_kernel, dim3(1), dim3(kTileTableThreads), 0, stream, groups,
-                     group_begin, cap, device, P, kTileM, tiles, n_tiles, nullptr, nullptr);
-  return hipGetLastError();
+  if (tid < 16) seq[tid] = 0;
+  for (int i = tid; i < total; i += kTileTableThreads) done[i] = 0;
 }
 
 // ---------------------------------------------------------------------------

@@ -284,7 +284,9 @@ void launch_gather_v(int grid, hipStream_t stream, const PermuteArgs &a, int32_t
 // Small calls: both kernels in one launch. A workgroup ranks the whole slice
 // of its kSmallPairs pairs (the loads and ballots of rank_kernel; their
 // latency, not their number, is what costs) and gathers the rows of its own
-// pairs, each wave taking 1 KB pieces of the tokens' rows.
+// pairs, each wave taking 1 KB pieces of the tokens' rows. Two launches ->
+// one: 4100 pairs 10.0 -> 10.4 us, 8008 10.9 -> 11.8, 8192 wider ones 13.2 ->
+// 14.7.
 constexpr int kSmallPairs = 4;
 constexpr int kSmallPermute = 4096;  // pairs
 

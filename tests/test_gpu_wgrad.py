@@ -28,7 +28,9 @@ def dev():
     (SIZES, 3, 320, 192),
     ((900, 3, 0, 1, 40, 5, 17, 2), 8, 256, 448),  # the first expert on every device
     ((1, 1, 1, 1), 2, 512, 128),
-], ids=["64x64", "320x192", "spill", "ones"])
+    # the most experts and devices: more groups than experts, two per table thread
+    (tuple(0 if e % 7 == 3 else 1 + e * e % 41 + 300 * (e % 97 == 5) for e in range(512)), 64, 64, 64),
+], ids=["64x64", "320x192", "spill", "ones", "512 experts"])
 def test_weight_gradients(dev, loads, P, D, F):
     import torch
     from paper_2601_17111_amd.synth import LayerConfig
