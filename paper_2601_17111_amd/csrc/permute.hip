@@ -22,26 +22,17 @@
 
 namespace llep {
 
-struct RankArgs {
-  const int32_t *ids;
-  const float *gates;
-  int64_t R;
-  int32_t E, max_chunks, n_tiles;
-  const int32_t *rank_base, *chunks, *chunk_row, *expert_chunk_begin;
-  int32_t *pair_row, *row_pair;
-  float *gate_perm;
-};
-
 // The row of pair p = 256 slice + threadIdx.x, or -1 (invalid id, no chunk,
 // past the end), and the pair's gate. 256 threads; smem: rank_lds bytes.
-__device__ __forceinline__ int32_t rank_slice(const RankArgs &a, int64_t slice, int32_t *smem,
-                                              float &gv) {
-  const int64_t R = a.R;
-  const int32_t E = a.E, max_chunks = a.max_chunks, n_tiles = a.n_tiles;
-  const int32_t *__restrict__ ids = a.ids, *__restrict__ rank_base = a.rank_base;
-  const float *__restrict__ gates = a.gates;
-  const int32_t *__restrict__ chunks = a.chunks, *__restrict__ chunk_row = a.chunk_row;
-  const int32_t *__restrict__ expert_chunk_begin = a.expert_chunk_begin;
+// Separate restrict parameters in every kernel that calls this: from one
+// struct of them the compiler issues the chunk table's loads before the counts'
+// and waits for all of them at the first use (rank and gather of 8008 pairs of
+// 128 experts 10.6 -> 11.1 us).
+__device__ __forceinline__ int32_t rank_slice(
+    const int32_t *__restrict__ ids, const float *__restrict__ gates, int64_t R, int32_t E,
+    int32_t max_chunks, int32_t n_tiles, const int32_t *__restrict__ rank_base,
+    const int32_t *__restrict__ chunks, const int32_t *__restrict__ chunk_row,
+    const int32_t *__restrict__ expert_chunk_begin, int64_t slice, int32_t *smem, float &gv) {
   // LDS: per-wave bases [kRankWaves][E], then the plan's chunk table
   // (expert_chunk_begin [E+1]; start, end, first row per chunk)
   int32_t *wbase = smem;
@@ -156,20 +147,30 @@ __device__ __forceinline__ int32_t rank_slice(const RankArgs &a, int64_t slice, 
   return inside ? c_row[c] + (r - c_start[c]) : -1;
 }
 
-__device__ __forceinline__ void write_row(const RankArgs &a, int64_t p, int32_t row, float gv) {
-  if (p >= a.R) return;
-  a.pair_row[p] = row;
-  if (row >= 0 && row < a.R) {
-    a.row_pair[row] = int32_t(p);
-    a.gate_perm[row] = gv;
+__device__ __forceinline__ void write_row(int64_t p, int64_t R, int32_t row, float gv,
+                                          int32_t *__restrict__ pair_row,
+                                          int32_t *__restrict__ row_pair,
+                                          float *__restrict__ gate_perm) {
+  if (p >= R) return;
+  pair_row[p] = row;
+  if (row >= 0 && row < R) {
+    row_pair[row] = int32_t(p);
+    gate_perm[row] = gv;
   }
 }
 
-__global__ __launch_bounds__(256) void rank_kernel(RankArgs a) {
+__global__ __launch_bounds__(256) void rank_kernel(
+    const int32_t *__restrict__ ids, const float *__restrict__ gates, int64_t R,
+    int32_t E, int32_t max_chunks, int32_t n_tiles, const int32_t *__restrict__ rank_base,
+    const int32_t *__restrict__ chunks, const int32_t *__restrict__ chunk_row,
+    const int32_t *__restrict__ expert_chunk_begin, int32_t *__restrict__ pair_row,
+    int32_t *__restrict__ row_pair, float *__restrict__ gate_perm) {
   extern __shared__ int32_t smem[];
   float gv;
-  const int32_t row = rank_slice(a, blockIdx.x, smem, gv);
-  write_row(a, int64_t(blockIdx.x) * kRankSub + threadIdx.x, row, gv);
+  const int32_t row = rank_slice(ids, gates, R, E, max_chunks, n_tiles, rank_base, chunks,
+                                 chunk_row, expert_chunk_begin, blockIdx.x, smem, gv);
+  write_row(int64_t(blockIdx.x) * kRankSub + threadIdx.x, R, row, gv, pair_row, row_pair,
+            gate_perm);
 }
 
 // Access choices, measured on MI355X with the gpt-oss-120b, deepseek-v3 and
@@ -290,22 +291,27 @@ void launch_gather_v(int grid, hipStream_t stream, const PermuteArgs &a, int32_t
 constexpr int kSmallPairs = 4;
 constexpr int kSmallPermute = 4096;  // pairs
 
-__global__ __launch_bounds__(256) void rank_gather_kernel(RankArgs a, const i32x4 *__restrict__ x,
-                                                          i32x4 *__restrict__ x_perm, int32_t K,
-                                                          int32_t vecs) {
+__global__ __launch_bounds__(256) void rank_gather_kernel(
+    const int32_t *__restrict__ ids, const float *__restrict__ gates, int64_t R,
+    int32_t E, int32_t max_chunks, int32_t n_tiles, const int32_t *__restrict__ rank_base,
+    const int32_t *__restrict__ chunks, const int32_t *__restrict__ chunk_row,
+    const int32_t *__restrict__ expert_chunk_begin, int32_t *__restrict__ pair_row,
+    int32_t *__restrict__ row_pair, float *__restrict__ gate_perm, const i32x4 *__restrict__ x,
+    i32x4 *__restrict__ x_perm, int32_t K, int32_t vecs) {
   extern __shared__ int32_t smem[];
   __shared__ int32_t rows[kRankSub];
   static_assert(kRankSub % kSmallPairs == 0, "a workgroup's pairs are of one slice");
   const int64_t p0 = int64_t(blockIdx.x) * kSmallPairs;
   const int64_t slice = p0 / kRankSub;
   float gv;
-  const int32_t row = rank_slice(a, slice, smem, gv);
+  const int32_t row = rank_slice(ids, gates, R, E, max_chunks, n_tiles, rank_base, chunks,
+                                 chunk_row, expert_chunk_begin, slice, smem, gv);
   rows[threadIdx.x] = row;
   const int64_t p = slice * kRankSub + threadIdx.x;
-  if (p >= p0 && p < p0 + kSmallPairs) write_row(a, p, row, gv);
+  if (p >= p0 && p < p0 + kSmallPairs) write_row(p, R, row, gv, pair_row, row_pair, gate_perm);
   __syncthreads();
   const int lane = lane_id(), w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  const int n = int(min(int64_t(kSmallPairs), a.R - p0)), at = int(p0 - slice * kRankSub);
+  const int n = int(min(int64_t(kSmallPairs), R - p0)), at = int(p0 - slice * kRankSub);
   for (int v0 = w * kWave; v0 < vecs; v0 += kRankWaves * kWave) {
     const int v = v0 + lane;
     if (v >= vecs) break;
@@ -319,7 +325,7 @@ __global__ __launch_bounds__(256) void rank_gather_kernel(RankArgs a, const i32x
       if (i >= n) break;
       if (i > 0 && (p0 + i) % K != 0) val[i] = val[i - 1];
       const int32_t r = __builtin_amdgcn_readfirstlane(rows[at + i]);
-      if (r >= 0 && r < a.R) x_perm[int64_t(r) * vecs + v] = val[i];
+      if (r >= 0 && r < R) x_perm[int64_t(r) * vecs + v] = val[i];
     }
   }
 }
@@ -327,18 +333,20 @@ __global__ __launch_bounds__(256) void rank_gather_kernel(RankArgs a, const i32x
 hipError_t launch_permute(const PermuteArgs &a, hipStream_t stream) {
   if (a.R == 0) return hipSuccess;
   const size_t lds = (size_t(kRankWaves + 1) * a.E + 1 + 3 * size_t(kMaxChunks)) * sizeof(int32_t);
-  const RankArgs r = {a.ids, a.gates, a.R, a.E, a.max_chunks, a.n_tiles, a.plan.rank_base,
-                      a.plan.chunks, a.plan.chunk_row, a.plan.expert_chunk_begin, a.pair_row,
-                      a.row_pair, a.gate_perm};
   const int32_t vecs = int32_t((int64_t(a.D) * a.elem_bytes) / 16);
   if (a.R <= kSmallPermute) {
     hipLaunchKernelGGL(rank_gather_kernel, dim3((a.R + kSmallPairs - 1) / kSmallPairs), dim3(256),
-                       lds, stream, r, static_cast<const i32x4 *>(a.x),
-                       static_cast<i32x4 *>(a.x_perm), a.K, vecs);
+                       lds, stream, a.ids, a.gates, a.R, a.E, a.max_chunks, a.n_tiles,
+                       a.plan.rank_base, a.plan.chunks, a.plan.chunk_row,
+                       a.plan.expert_chunk_begin, a.pair_row, a.row_pair, a.gate_perm,
+                       static_cast<const i32x4 *>(a.x), static_cast<i32x4 *>(a.x_perm), a.K, vecs);
     return hipGetLastError();
   }
   const int64_t slices = (a.R + kRankSub - 1) / kRankSub;
-  hipLaunchKernelGGL(rank_kernel, dim3(slices), dim3(256), lds, stream, r);
+  hipLaunchKernelGGL(rank_kernel, dim3(slices), dim3(256), lds, stream, a.ids, a.gates,
+                     a.R, a.E, a.max_chunks, a.n_tiles, a.plan.rank_base, a.plan.chunks,
+                     a.plan.chunk_row, a.plan.expert_chunk_begin, a.pair_row, a.row_pair,
+                     a.gate_perm);
   hipError_t err = hipGetLastError();
   if (err != hipSuccess) return err;
   const int64_t blocks = (a.T * ((vecs + kWave - 1) / kWave) + kGatherWaves - 1) / kGatherWaves;
