@@ -17,6 +17,7 @@
 // gather_kernel  one wavefront per 1 KB piece of a token's row (64 16-byte
 //                vectors): reads it once and writes it to the K rows of the
 //                token's pairs.
+// rank_gather_kernel  both in one launch, for small calls.
 #include "common.h"
 #include "kernels.h"
 
@@ -24,15 +25,18 @@ namespace llep {
 
 // The row of pair p = 256 slice + threadIdx.x, or -1 (invalid id, no chunk,
 // past the end), and the pair's gate. 256 threads; smem: rank_lds bytes.
+// more_loads(): the caller's own loads, requested behind the ones made here.
 // Separate restrict parameters in every kernel that calls this: from one
 // struct of them the compiler issues the chunk table's loads before the counts'
 // and waits for all of them at the first use (rank and gather of 8008 pairs of
 // 128 experts 10.6 -> 11.1 us).
+template <typename Loads>
 __device__ __forceinline__ int32_t rank_slice(
     const int32_t *__restrict__ ids, const float *__restrict__ gates, int64_t R, int32_t E,
     int32_t max_chunks, int32_t n_tiles, const int32_t *__restrict__ rank_base,
     const int32_t *__restrict__ chunks, const int32_t *__restrict__ chunk_row,
-    const int32_t *__restrict__ expert_chunk_begin, int64_t slice, int32_t *smem, float &gv) {
+    const int32_t *__restrict__ expert_chunk_begin, int64_t slice, int32_t *smem, float &gv,
+    Loads &&more_loads) {
   // LDS: per-wave bases [kRankWaves][E], then the plan's chunk table
   // (expert_chunk_begin [E+1]; start, end, first row per chunk)
   int32_t *wbase = smem;
@@ -84,6 +88,7 @@ __device__ __forceinline__ int32_t rank_slice(
     ce[k] = chunks[4 * cc + 3];
     cr[k] = chunk_row[cc];
   }
+  more_loads();
   __builtin_amdgcn_sched_barrier(0);  // the loads above issue together
   uint32_t ev = uint32_t(E);  // sentinel: past the end or invalid
   gv = 0.0f;
@@ -168,7 +173,7 @@ __global__ __launch_bounds__(256) void rank_kernel(
   extern __shared__ int32_t smem[];
   float gv;
   const int32_t row = rank_slice(ids, gates, R, E, max_chunks, n_tiles, rank_base, chunks,
-                                 chunk_row, expert_chunk_begin, blockIdx.x, smem, gv);
+                                 chunk_row, expert_chunk_begin, blockIdx.x, smem, gv, [] {});
   write_row(int64_t(blockIdx.x) * kRankSub + threadIdx.x, R, row, gv, pair_row, row_pair,
             gate_perm);
 }
@@ -282,14 +287,26 @@ void launch_gather_v(int grid, hipStream_t stream, const PermuteArgs &a, int32_t
                      a.pair_row, a.T, a.K, vecs, a.R);
 }
 
-// Small calls: both kernels in one launch. A workgroup ranks the whole slice
-// of its kSmallPairs pairs (the loads and ballots of rank_kernel; their
-// latency, not their number, is what costs) and gathers the rows of its own
-// pairs, each wave taking 1 KB pieces of the tokens' rows. Two launches ->
-// one: 4100 pairs 10.0 -> 10.4 us, 8008 10.9 -> 11.8, 8192 wider ones 13.2 ->
-// 14.7.
+// Small calls: both kernels in one launch, bound by latency. A workgroup ranks
+// the whole slice of its kSmallPairs pairs (the loads and ballots of
+// rank_kernel; their latency, not their number, is what costs) and gathers the
+// rows of its own pairs, each wave taking 1 KB pieces of the tokens' rows. The
+// pieces are requested with the rank's own loads, kSmallPieces per token at
+// once: requested one after another behind the rank, rows of more than four
+// pieces cost a memory round trip each (8 pairs of D = 7168, K = 1: 9.9 us, two
+// launches 4.9, now 4.2; 512 pairs, K = 8: 9.5, 6.5 and 5.6).
 constexpr int kSmallPairs = 4;
-constexpr int kSmallPermute = 4096;  // pairs
+constexpr int kSmallPieces = 4;  // of a token's row, per wave, in flight
+// Up to how many pairs, by the width of a row. Four workgroups run on a CU, so
+// up to 4096 pairs all of them run at once; from one piece per wave on (vecs >=
+// 4 * 64) one launch gains up to there (two launches -> one, us, at 32 / 512
+// experts; D = 2048, K = 8: 4096 pairs 8.4 -> 7.6 / 9.0 -> 8.7, 4608 pairs
+// 8.7 -> 9.3 / 9.3 -> 10.3; D = 7168, K = 8: 15.1 -> 12.8 / 15.6 -> 13.5 and
+// 15.8 -> 15.2 / 16.2 -> 16.4). Narrower rows leave less to overlap with the
+// ranking, which grows with the workgroups (D = 64, K = 8: 3072 pairs 5.8 ->
+// 5.3 / 6.3 -> 5.9, 3584 pairs 5.8 -> 5.9 / 6.3 -> 6.7, 4096 pairs 5.8 -> 6.0 /
+// 6.3 -> 6.9).
+constexpr int kSmallPermuteWide = 4096, kSmallPermuteNarrow = 3072;
 
 __global__ __launch_bounds__(256) void rank_gather_kernel(
     const int32_t *__restrict__ ids, const float *__restrict__ gates, int64_t R,
@@ -304,29 +321,60 @@ __global__ __launch_bounds__(256) void rank_gather_kernel(
   const int64_t p0 = int64_t(blockIdx.x) * kSmallPairs;
   const int64_t slice = p0 / kRankSub;
   float gv;
+  const int lane = lane_id(), w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int n = int(min(int64_t(kSmallPairs), R - p0)), at = int(p0 - slice * kRankSub);
+  // pair i starts a token (own[i]) or has the row of the pair before it
+  const i32x4 *src[kSmallPairs];
+  bool own[kSmallPairs];
+#pragma unroll
+  for (int i = 0; i < kSmallPairs; ++i) {
+    const int t = (int(p0) + i) / K;
+    src[i] = x + int64_t(t) * vecs;
+    own[i] = i < n && (i == 0 || t != (int(p0) + i - 1) / K);
+  }
+  // the wave's piece j of the kSmallPieces from vector v0 on, one per token
+  constexpr int kStep = kRankWaves * kWave;
+  i32x4 val[kSmallPieces][kSmallPairs];
+  auto load = [&](int v0) {
+#pragma unroll
+    for (int j = 0; j < kSmallPieces; ++j) {
+      if (v0 + j * kStep + w * kWave >= vecs) break;
+      const int v = min(v0 + j * kStep + w * kWave + lane, vecs - 1);
+#pragma unroll
+      for (int i = 0; i < kSmallPairs; ++i)
+        if (own[i]) val[j][i] = src[i][v];
+    }
+  };
   const int32_t row = rank_slice(ids, gates, R, E, max_chunks, n_tiles, rank_base, chunks,
-                                 chunk_row, expert_chunk_begin, slice, smem, gv);
+                                 chunk_row, expert_chunk_begin, slice, smem, gv,
+                                 [&] { load(0); });
   rows[threadIdx.x] = row;
   const int64_t p = slice * kRankSub + threadIdx.x;
   if (p >= p0 && p < p0 + kSmallPairs) write_row(p, R, row, gv, pair_row, row_pair, gate_perm);
   __syncthreads();
-  const int lane = lane_id(), w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  const int n = int(min(int64_t(kSmallPairs), R - p0)), at = int(p0 - slice * kRankSub);
-  for (int v0 = w * kWave; v0 < vecs; v0 += kRankWaves * kWave) {
-    const int v = v0 + lane;
-    if (v >= vecs) break;
-    // the tokens' pieces are requested together, one per token
-    i32x4 val[kSmallPairs];
+  int32_t r[kSmallPairs];
 #pragma unroll
-    for (int i = 0; i < kSmallPairs; ++i)
-      if (i < n && (i == 0 || (p0 + i) % K == 0)) val[i] = x[(p0 + i) / K * vecs + v];
+  for (int i = 0; i < kSmallPairs; ++i)
+    r[i] = i < n ? __builtin_amdgcn_readfirstlane(rows[at + i]) : -1;
+  for (int v0 = 0;;) {
+    // every load is waited for here, so that no store is waited for below
 #pragma unroll
-    for (int i = 0; i < kSmallPairs; ++i) {
-      if (i >= n) break;
-      if (i > 0 && (p0 + i) % K != 0) val[i] = val[i - 1];
-      const int32_t r = __builtin_amdgcn_readfirstlane(rows[at + i]);
-      if (r >= 0 && r < R) x_perm[int64_t(r) * vecs + v] = val[i];
+    for (int j = 0; j < kSmallPieces; ++j)
+#pragma unroll
+      for (int i = 0; i < kSmallPairs; ++i) asm volatile("" : "+v"(val[j][i]));
+#pragma unroll
+    for (int j = 0; j < kSmallPieces; ++j) {
+      const int v = v0 + j * kStep + w * kWave + lane;
+      if (v >= vecs) break;
+#pragma unroll
+      for (int i = 0; i < kSmallPairs; ++i) {
+        if (i > 0 && !own[i]) val[j][i] = val[j][i - 1];
+        if (r[i] >= 0 && r[i] < R) x_perm[int64_t(r[i]) * vecs + v] = val[j][i];
+      }
     }
+    v0 += kSmallPieces * kStep;
+    if (v0 >= vecs) break;
+    load(v0);
   }
 }
 
@@ -334,7 +382,7 @@ hipError_t launch_permute(const PermuteArgs &a, hipStream_t stream) {
   if (a.R == 0) return hipSuccess;
   const size_t lds = (size_t(kRankWaves + 1) * a.E + 1 + 3 * size_t(kMaxChunks)) * sizeof(int32_t);
   const int32_t vecs = int32_t((int64_t(a.D) * a.elem_bytes) / 16);
-  if (a.R <= kSmallPermute) {
+  if (a.R <= (vecs >= kRankWaves * kWave ? kSmallPermuteWide : kSmallPermuteNarrow)) {
     hipLaunchKernelGGL(rank_gather_kernel, dim3((a.R + kSmallPairs - 1) / kSmallPairs), dim3(256),
                        lds, stream, a.ids, a.gates, a.R, a.E, a.max_chunks, a.n_tiles,
                        a.plan.rank_base, a.plan.chunks, a.plan.chunk_row,

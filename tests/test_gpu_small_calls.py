@@ -1,7 +1,9 @@
-"""Plan and permutation of calls of at most 4096 pairs (one launch each): at
-the edges of their slices (256 pairs), tiles (1024) and range, for experts on
-both sides of the thread-count choice (256), rows of less than one and of
-several 1 KB pieces, and invalid ids; bit-exact against the oracle."""
+"""Plan and permutation of small calls (one launch each, up to 4096 pairs; the
+permutation of rows of less than 4 KB up to 3072): at the edges of their slices
+(256 pairs), tiles (1024) and ranges, for few and many experts, rows of less
+than one 1 KB piece, of several, and of more than the 16 that are in flight at
+once, one to four tokens per workgroup, and invalid ids; bit-exact against the
+oracle."""
 
 import math
 
@@ -25,7 +27,9 @@ def dev():
     (257, 1, 256, 8, 136, "bf16"), (51, 5, 255, 5, 4104, "bf16"), (341, 3, 12, 4, 72, "f32"),
     (128, 8, 512, 64, 72, "bf16"), (205, 5, 257, 1, 72, "bf16"), (819, 5, 64, 8, 264, "bf16"),
     (512, 8, 512, 8, 72, "bf16"), (4096, 1, 256, 64, 8, "f32"), (4097, 1, 256, 64, 8, "f32"),
-    (60, 67, 32, 4, 72, "bf16"),
+    (60, 67, 32, 4, 72, "bf16"), (3072, 1, 32, 4, 72, "bf16"), (3073, 1, 32, 4, 72, "bf16"),
+    (4096, 1, 16, 4, 2048, "bf16"), (4097, 1, 16, 4, 2048, "bf16"), (9, 1, 8, 4, 8192, "bf16"),
+    (9, 2, 8, 4, 8200, "bf16"), (7, 3, 8, 4, 8200, "f32"), (33, 4, 8, 4, 7168, "bf16"),
 ])
 @pytest.mark.parametrize("mode", ["llep", "ep"])
 def test_small_plan_and_permutation(dev, T, K, E, P, D, dtype, mode):
