@@ -5,6 +5,7 @@
 #include <stdint.h>
 #include <string.h>
 
+#include <algorithm>
 #include <string>
 
 #include "kernels.h"
@@ -199,6 +200,7 @@ static int grouped_ffn(const llep_plan_params *params, const llep_plan_buffers *
     return fail(LLEP_E_WORKSPACE, "workspace not 256-byte aligned");
   llep::FfnArgs a = {};
   a.R = params->T * params->K;
+  a.device_rows = params->mode == LLEP_MODE_LLEP ? std::min(a.R, params->capacity) : a.R;
   a.P = params->P;
   a.E = params->E;
   a.D = D;

@@ -439,7 +439,7 @@ hipError_t launch_grouped_ffn(const FfnArgs &a, hipStream_t stream) {
   int4 *tiles = reinterpret_cast<int4 *>(ws + L.tiles_off);
   int32_t *done = reinterpret_cast<int32_t *>(ws + L.done_off);
   void *act = ws + L.act_off;
-  if (a.dtype == LLEP_BF16 && use_stream_ffn(a.R, a.E, a.D, a.F))
+  if (a.dtype == LLEP_BF16 && use_stream_ffn(a))
     return launch_stream_ffn(a, act, stream);
   if (a.dtype == LLEP_BF16) {
     const int grid = (cu_count() + 7) / 8 * 8;  // one workgroup per CU, XCD-balanced

@@ -65,6 +65,7 @@ hipError_t launch_combine(const CombineArgs &a, hipStream_t stream);
 
 struct FfnArgs {
   int64_t R;
+  int64_t device_rows;  // rows that one device can be expected to hold at most
   int32_t P, E, D, F, device;
   llep_dtype dtype;
   const int32_t *groups, *group_begin;
@@ -81,7 +82,7 @@ hipError_t launch_grouped_ffn(const FfnArgs &a, hipStream_t stream);
 // The bf16 forward of calls of few rows (stream_ffn.hip): R pairs over all
 // devices, at most kStreamRows; act: the workspace's activation.
 constexpr int kStreamRows = 4096;
-bool use_stream_ffn(int64_t R, int32_t E, int32_t D, int32_t F);
+bool use_stream_ffn(const FfnArgs &a);
 hipError_t launch_stream_ffn(const FfnArgs &a, void *act, hipStream_t stream);
 // The float32 forward and backward (ffn_f32.hip); act [R][F] and dgu [R][2F]
 // by x_perm row, in the workspace.

@@ -550,16 +550,43 @@ __attribute__((amdgpu_waves_per_eu(1, 1))) void stream_ffn_kernel(StreamArgs a) 
                                 u0[4], 1, k[4]);
 }
 
-// The weight stream wins, or is even with the tiles, on every routing measured
-// up to 24 rows per expert on average (at 24, uniform / hot: gpt-oss-20b 266 /
-// 282-293 us against 320 / 316-334, qwen3-30b-a3b 228 / 227-245 against 242 /
-// 230-242, 64 experts of 2048 x 1408 201 / 203-216 against 219 / 210-225; at
-// 48 with one expert taking 90% of the rows 375 against 360). It also wins
-// while the whole call is short, since a tile of gemm.h takes 60-100 us from
-// end to end however few there are: up to D F R = 5 10^9 (16 experts of
-// 1024 x 768, R = 4096: 56-65 us against 92-94).
-bool use_stream_ffn(int64_t R, int32_t E, int32_t D, int32_t F) {
-  return R <= kStreamRows && (R <= int64_t(24) * E || R * D * F <= int64_t(5000000000));
+// Where the weight stream runs. Times are of the tiles / the stream in us, with
+// uniform, Zipf(1.2) and hot routings (50-95% of the rows on one to four
+// experts) on 1 and 8 devices; the routing is not known here.
+//
+// Every group: the tiles take 60-100 us from end to end however few there are,
+// and then work at the higher rate on a hot expert's rows.
+// - Up to 24 rows per expert on average and 1024 rows the stream wins or is
+//   even (2880 x 2880: 32 experts, 768 rows, uniform 308 / 260, Zipf 311 / 283;
+//   64 experts, 896 rows, Zipf on one device 519 / 512; 128 experts, 1024 rows,
+//   80% on four 851 / 815). At the line up to 5% are lost with 95% of the rows
+//   on one expert, and on some routings of 7168 x 2048 layers, both on one
+//   device (128 experts of 2880 x 2880, 1024 rows, 95%: 342 / 356; 64 of 7168 x
+//   2048, 896 rows, Zipf: 877 / 913).
+//   Beyond it every skewed routing loses: 64 of 7168 x 2048 with 1536 rows 926 /
+//   967 (Zipf) and 661 / 757 (95%), 128 of 2880 x 2880 with 3072 rows 1132 /
+//   1146 and 781 / 854, for 2-7% that a uniform one gains.
+// - While the whole call is short it wins whatever the rows per expert, down to
+//   a single one: up to D F R = 5 10^9 (16 experts of 1024 x 768, R = 4096:
+//   92-94 / 56-65; one expert of 2880 x 2880, R = 602: 133 / 107; 64 of 2048 x
+//   768, R = 3178, 90% on one: 162 / 145), with more than 64 experts up to 4
+//   10^9 (128 of 2048 x 768, Zipf: R = 2176 216 / 217, R = 3072 229 / 234).
+//
+// One device of several: its range is a part of the rows and experts, so the
+// tiles have still less to fill the chip with (the device of most rows of 8, 64
+// experts of 2880 x 2880, 1536 rows, 80% on one expert: 161 / 96). Up to the
+// rows per expert or the size of above the stream is kept while the rows that
+// the device can hold, the plan's capacity or for standard expert parallelism
+// all of them, have D F rows <= 2 10^10 (all rows of 128 experts of 2880 x 2880
+// on 8 devices, standard plan, Zipf: 2048 rows 233 / 230, 3072 rows 252 / 256
+// and 259 / 292 with 95% on one expert).
+bool use_stream_ffn(const FfnArgs &a) {
+  if (a.R > kStreamRows) return false;
+  const bool few = a.R <= int64_t(24) * a.E;
+  const int64_t weight = int64_t(a.D) * a.F, work = weight * a.R;
+  if (a.device >= 0 && a.P > 1)
+    return (few || work <= int64_t(5000000000)) && weight * a.device_rows <= int64_t(20000000000);
+  return (few && a.R <= 1024) || work <= (a.E <= 64 ? int64_t(5000000000) : int64_t(4000000000));
 }
 
 hipError_t launch_stream_ffn(const FfnArgs &a, void *act, hipStream_t stream) {

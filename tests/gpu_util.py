@@ -65,6 +65,18 @@ def assert_plan_equal(got: dict, info: dict, ref: "oracle.PlanResult"):
     assert info["total_rows"] == sum(ref.device_rows)
 
 
+def mark_workspace(layer):
+    """Before a bf16 forward: ran_tiles() then tells which kernels ran."""
+    layer.workspace[:4].fill_(0xa5)
+
+
+def ran_tiles(layer) -> bool:
+    """Whether the forward since mark_workspace() went through the 256-row
+    tiles, which keep their count at the start of the workspace; the weight
+    stream leaves it alone."""
+    return bool((layer.workspace[:4] != 0xa5).any())
+
+
 def rel_err(got: np.ndarray, want: np.ndarray) -> float:
     """max |got - want| / max |want| (over the compared entries)."""
     den = np.abs(want).max()

@@ -10,7 +10,7 @@ import numpy as np
 import pytest
 
 import oracle
-from gpu_util import LayerRun, device, rel_err
+from gpu_util import LayerRun, device, mark_workspace, ran_tiles, rel_err
 
 pytestmark = pytest.mark.gpu
 
@@ -102,3 +102,43 @@ def test_stream_one_device_and_plans(dev, loads, P):
         at += rows[d]
     L.set_mode("ep")
     assert torch.equal(run.forward(-1), y)
+
+
+@pytest.mark.parametrize("T,E,P,D,F,tiles", [
+    (1024, 64, 8, 2560, 2048, (0, 0, 0)),  # 24 rows per expert: up to 1024 rows
+    (1025, 64, 8, 2560, 2048, (1, 0, 0)),
+    (1536, 64, 1, 2560, 2048, (1, 1, 1)),  # the only device: as all of them
+    (2441, 64, 8, 2560, 768, (0, 0, 0)),   # more rows: D F R up to 5 10^9
+    (2560, 64, 8, 2560, 768, (1, 1, 1)),
+    (2029, 72, 8, 2560, 768, (0, 0, 0)),   # 4 10^9 with more than 64 experts
+    (2048, 72, 8, 2560, 768, (1, 0, 0)),
+    (4096, 172, 4, 2560, 1920, (1, 0, 1)),  # one device's rows: 2 10^10
+], ids=lambda v: str(v) if isinstance(v, int) else "")
+def test_dispatch(dev, T, E, P, D, F, tiles):
+    """Both sides of every line of the rule that chooses between the stream and
+    the tiles, for all devices at once, one device of an LLEP and one of a
+    standard plan (tiles); whatever ran, the same bits."""
+    import torch
+    from paper_2601_17111_amd.synth import LayerConfig
+    cfg = LayerConfig(f"route-T{T}-E{E}", T=T, D=D, F=F, E=E, K=1, P=P, alpha=Fraction(11, 10),
+                      dtype="bf16", routing=("hot", 0.8, 1))
+    run = LayerRun(cfg, 3, dev)
+    L = run.layer
+    out = {}
+    for mode, device_tiles in (("llep", tiles[1]), ("ep", tiles[2])):
+        L.set_mode(mode)
+        mark_workspace(L)
+        run.forward(-1)
+        assert ran_tiles(L) == tiles[0], mode
+        out[mode] = L.out_perm[L.pair_row.reshape(-1).long()].clone()
+        full = L.out_perm.clone()
+        d = L.bufs.info_dict()["max_device"]
+        at = int(L.bufs.device_rows[:d].sum())
+        n = int(L.bufs.device_rows[d])
+        L.out_perm.fill_(float("nan"))
+        mark_workspace(L)
+        L.ffn(run.gu, run.dn, d)
+        torch.cuda.synchronize()
+        assert ran_tiles(L) == device_tiles, mode
+        assert torch.equal(L.out_perm[at:at + n], full[at:at + n])
+    assert torch.equal(out["llep"], out["ep"])
