@@ -320,7 +320,7 @@ int llep_pack_weights_backward(int32_t E, int32_t D, int32_t F, llep_dtype dtype
  * first, then the groups on other devices by increasing device index. For
  * device == d these are d's partial gradients; for device == -1 they are the
  * totals each native device holds after the gradient return. Experts without
- * a group in the range are not written; rows outside the range are not
+ * rows in the range are not written; rows outside the range are not
  * written. Weights are the llep_pack_weights (w_gate_up_packed) and
  * llep_pack_weights_backward outputs. bf16 uses matrix cores and rounds g,
  * u, dg, du and act to bf16 once each; f32 is a plain reference-precision
@@ -350,7 +350,7 @@ int llep_grouped_ffn_backward(const llep_plan_params *params,
                               float *dw_up, float *dw_down, void *workspace,
                               size_t workspace_bytes, hipStream_t stream);
 
-/* Zeros for the weight gradients of the experts without a group in the range
+/* Zeros for the weight gradients of the experts without rows in the range
  * of `device` (or of all devices when device == -1): the experts that
  * llep_grouped_ffn_backward on the same plan and device does not write, so
  * that the two calls together write every element of dw_gate, dw_up and

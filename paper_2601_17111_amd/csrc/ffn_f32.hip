@@ -277,7 +277,7 @@ __device__ __forceinline__ void f32_wgrad_tile(const F32Wgrad &g, const F32Range
     for (int g0 = lo; g0 < hi; g0 += kWave) {
       const int32_t *p = r.groups + 4 * min(g0 + lane, hi - 1);
       const int d = p[0], ge = p[1], row = p[2], n = p[3];
-      uint64_t mine = __ballot(g0 + lane < hi && ge == e && (d == nat) == (pass == 0));
+      uint64_t mine = __ballot(g0 + lane < hi && n > 0 && ge == e && (d == nat) == (pass == 0));
       while (mine) {
         const int l = __builtin_ctzll(mine);
         mine &= mine - 1;
@@ -285,7 +285,7 @@ __device__ __forceinline__ void f32_wgrad_tile(const F32Wgrad &g, const F32Range
         rows_of(__shfl(row, l), __shfl(n, l));
       }
     }
-  if (!any) return;  // experts without a group in the range are not written
+  if (!any) return;  // experts without rows in the range are not written
   const int row = m0 + wr * 32 + (lane & 31), col0 = n0 + wc * 32;
   float *C = g.C;
   int ld = g.N, col = col0;

@@ -73,8 +73,8 @@ size_t ffn_backward_workspace_bytes(int64_t R, int32_t E, int32_t P, int32_t D, 
 // step 346.9 -> 342.4 us).
 // Workgroup 1: the tile list of gemm.h's launches, one entry (group, m-tile,
 // padded first row of the group) per kTileM rows of each group of the range.
-// Workgroup 0: for the groups [lo, hi) of the range, sorted by expert and
-// within an expert in gradient-return order: their first x_perm row, first
+// Workgroup 0: for the groups [lo, hi) of the range that have rows, sorted by
+// expert and within an expert in gradient-return order: their first x_perm row, first
 // 16-row block of padded rows, and rows; and the experts present with their
 // first group and 32-row slices (each group's rounded up), most slices first
 // (ties: lower expert id), and how many of them have at least long_slices
@@ -158,7 +158,8 @@ __global__ __launch_bounds__(kTableThreads) void bwd_table_kernel(
   for (int j = 0; j < kPer; ++j) {
     const int i = kPer * tid + j;
     if (i >= G) continue;
-    ge[i] = (e[j] << 1) | nat[j];
+    ge[i] = n[j] > 0 ? (e[j] << 1) | nat[j] : -1;  // (-1: no expert's)
+    if (n[j] == 0) continue;
     atomicAdd(&count[e[j]], 1);
     atomicAdd(&slices[e[j]], (n[j] + 31) / 32);
   }
@@ -181,7 +182,7 @@ __global__ __launch_bounds__(kTableThreads) void bwd_table_kernel(
 #pragma unroll
   for (int j = 0; j < kPer; ++j) {
     const int i = kPer * tid + j;
-    if (i >= G) continue;
+    if (i >= G || n[j] == 0) continue;
     const int32_t c = count[e[j]];
     int32_t at = c >> 1;
     if ((c & 1) && !nat[j]) {
@@ -286,7 +287,7 @@ void bwd_multi_kernel(GemmArgs g, WgArgs w, int32_t *counter) {
 }
 
 // ---------------------------------------------------------------------------
-// Zeros for the weight gradients of the experts without a group in the range
+// Zeros for the weight gradients of the experts without rows in the range
 // (the GEMMs write every element of the others). Bound by the stores to HBM;
 // every workgroup finds the absent experts from the group table itself (a few
 // loads) and takes 16 KB pieces of their three matrices in turn, so a few
@@ -313,7 +314,7 @@ __global__ __launch_bounds__(kZeroThreads) void zero_absent_kernel(
   __syncthreads();
   for (int g = lo + tid; g < hi; g += kZeroThreads) {
     const int e = groups[4 * g + 1];
-    if (e >= 0 && e < E) present[e] = 1;
+    if (e >= 0 && e < E && groups[4 * g + 3] > 0) present[e] = 1;
   }
   __syncthreads();
   if (tid < kWave) {  // in expert order, so that every workgroup has the same list

@@ -62,3 +62,41 @@ def test_weight_gradients(dev, loads, P, D, F):
         if e != bad:
             for a, b in zip(dw, again):
                 assert np.array_equal(a[e], b[e]), e
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_groups_without_rows(dev, dtype):
+    """A group table that a program has written itself may hold groups of no
+    rows: of an expert that has none, and beside an expert's other groups, on
+    its native device and on others. The same gradients, bit for bit."""
+    import torch
+    from paper_2601_17111_amd import binding as B
+    from paper_2601_17111_amd.synth import LayerConfig
+    loads, P, D, F = (260, 0, 40, 17, 0, 90, 5, 0), 4, 128, 192
+    cfg = LayerConfig("empty-groups", T=sum(loads), D=D, F=F, E=len(loads), K=1, P=P,
+                      alpha=Fraction(1), dtype=dtype, routing=("loads", tuple(loads)))
+    run = BwdRun(cfg, 1, dev)
+    want = run.backward(-1, save=True)
+    L = run.layer
+    n = L.bufs.info_dict()["n_groups"]
+    groups = L.bufs.groups[:n].cpu().tolist()
+    have = {(d, e) for d, e, _, _ in groups}
+    begin = L.bufs.device_rows.cpu().tolist()
+    more = [g for g in ([d, e, sum(begin[:d]), 0] for d in range(P) for e in range(cfg.E))
+            if (g[0], g[1]) not in have]
+    more = more[::2] + more[1::2]  # some of every device first
+    more = more[:2 * cfg.E + P - n]
+    assert any(loads[e] > 0 for _, e, _, _ in more) and any(loads[e] == 0 for _, e, _, _ in more)
+    table = sorted(groups + more, key=lambda g: g[:2])
+    L.bufs.groups[:len(table)] = torch.tensor(table, dtype=torch.int32, device=dev)
+    L.bufs.group_begin[:] = torch.tensor([sum(g[0] < d for g in table) for d in range(P + 1)],
+                                         dtype=torch.int32, device=dev)
+    for w in (L.dw_gate, L.dw_up, L.dw_down, L.dx_perm):
+        w.fill_(float("nan"))
+    L.ffn(run.gu, run.dn, -1, save_gate_up=True)
+    L.combine(run.gates)
+    got = L.backward(run.dy, run.gates, run.gu, run.gut, run.dnt, -1)
+    torch.cuda.synchronize()
+    assert not L.bufs.info_dict()["status"] & B.LLEP_STATUS_FFN_WAIT
+    for a, b in zip(want, got):
+        assert np.array_equal(a, b.float().cpu().numpy())
