@@ -19,7 +19,7 @@ import numpy as np
 import pytest
 
 import oracle
-from gpu_util import LayerRun, device, rel_err, report
+from gpu_util import LayerRun, device, mark_workspace, ran_tiles, rel_err, report
 
 pytestmark = pytest.mark.gpu
 
@@ -48,13 +48,17 @@ def _w64(W, e):
     return tuple(w.astype(np.float64) for w in W[e])
 
 
-@pytest.mark.parametrize("D,F", [(2880, 2880), (2048, 768)], ids=["down192", "down256"])
-def test_partial_mtiles_every_row(dev, D, F):
+# (rows enough that the call is not one of the weight stream's)
+@pytest.mark.parametrize("D,F,base", [(2880, 2880, 256), (2048, 768, 512)],
+                         ids=["down192", "down256"])
+def test_partial_mtiles_every_row(dev, D, F, base):
     import torch
-    cfg = _tile_cfg(D, F, 256)
+    cfg = _tile_cfg(D, F, base)
     run = LayerRun(cfg, 0, dev)
     L = run.layer
+    mark_workspace(L)
     run.forward(-1)
+    assert ran_tiles(L)
     out = L.out_perm.clone()
     info = L.bufs.info_dict()
     groups = L.bufs.groups[:info["n_groups"]].cpu().tolist()
@@ -136,11 +140,13 @@ def test_single_launch_waits_repeatable(dev, D, F):
     import torch
     from paper_2601_17111_amd import binding as B
     from paper_2601_17111_amd.synth import LayerConfig
-    cfg = LayerConfig(f"wait-D{D}-F{F}", T=700, D=D, F=F, E=16, K=4, P=4,
+    cfg = LayerConfig(f"wait-D{D}-F{F}", T=1100, D=D, F=F, E=16, K=4, P=4,
                       alpha=Fraction(11, 10), dtype="bf16", routing=("hot", 0.8, 1))
     run = LayerRun(cfg, 2, dev)
     L = run.layer
+    mark_workspace(L)
     y0 = run.forward(-1).clone()
+    assert ran_tiles(L)  # not the weight stream, which waits for nothing
     out0 = L.out_perm.clone()
     for _ in range(20):
         L.ffn(run.gu, run.dn, -1)
