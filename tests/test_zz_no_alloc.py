@@ -1,8 +1,9 @@
 """llep_grouped_ffn_noalloc through the C ABI: the same expert outputs as
 llep_grouped_ffn with a caller workspace (bit for bit, they share kernels),
-on two calls in a row with the second on a smaller layer, for one device's
-groups and for all devices; and a layer too large for the library's array is
-rejected on the host."""
+on calls in a row with the later ones on smaller layers, through the tiles
+(whose list and counters a call finds as the last one left them), the weight
+stream and both in turn, for one device's groups and for all devices; and a
+layer too large for the library's array is rejected on the host."""
 
 from fractions import Fraction
 
@@ -10,7 +11,7 @@ import numpy as np
 import pytest
 
 import oracle
-from gpu_util import LayerRun, device, rel_err
+from gpu_util import LayerRun, device, mark_workspace, ran_tiles, rel_err
 
 pytestmark = pytest.mark.gpu
 
@@ -26,11 +27,15 @@ def _cfg(T, dtype):
                        alpha=Fraction(11, 10), dtype=dtype, routing=("hot", 0.7, 2))
 
 
-@pytest.mark.parametrize("dtype", ["bf16", "f32"])
-def test_noalloc_matches_caller_workspace(dev, dtype):
+@pytest.mark.parametrize("dtype,sizes", [
+    ("bf16", (900, 300)), ("f32", (900, 300)),     # bf16: the stream, twice
+    ("bf16", (3000, 1100)),                        # the tiles, twice
+    ("bf16", (3000, 300, 1100)),                   # tiles, stream, tiles
+], ids=["bf16", "f32", "bf16-tiles", "bf16-both"])
+def test_noalloc_matches_caller_workspace(dev, dtype, sizes):
     import torch
     from paper_2601_17111_amd import binding as B
-    for T in (900, 300):  # the second call is on a smaller layer
+    for T in sizes:
         run = LayerRun(_cfg(T, dtype), 1, dev)
         L = run.layer
         L.plan(run.ids)
@@ -41,9 +46,11 @@ def test_noalloc_matches_caller_workspace(dev, dtype):
                                                   ) <= B.LLEP_NOALLOC_SCRATCH_BYTES
         for d in (info["max_device"], -1):  # all devices last: every row is then written
             L.out_perm.fill_(float("nan"))
+            mark_workspace(L)
             B.llep_grouped_ffn(L.params, L.bufs, d, L.x_perm, run.gu, run.dn, L.out_perm,
                                L.workspace)
             torch.cuda.synchronize()
+            assert ran_tiles(L) == (dtype == "bf16" and T > 1024)
             want = L.out_perm.clone()
             L.out_perm.fill_(float("nan"))
             B.llep_grouped_ffn_noalloc(L.params, L.bufs, d, L.x_perm, run.gu, run.dn,
