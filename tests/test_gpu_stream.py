@@ -1,8 +1,9 @@
 """The weight-streaming forward (calls of few rows) against the oracle and,
 bit for bit, against the tiled kernels: group sizes at the edges of its row
-classes (16, 32, 64, 128 and 256 rows) and of its pieces (256 rows), one k-stage
-per unit, column counts that leave a workgroup's last column units empty, and
-more units than workgroups."""
+classes (16, 32, 64, 128 and 256 rows) and of its pieces (256 rows, 64 where
+few), one k-stage per unit, column counts that leave a workgroup's last column
+units empty, more units than workgroups, and the most experts and devices; and
+the rule that chooses between the two."""
 
 from fractions import Fraction
 
@@ -33,16 +34,23 @@ def _cfg(loads, D, F, P=1):
     (EDGES, 64, 64),       # one stage per unit, one column unit of four per piece
     (EDGES, 320, 192),     # 10 output units: the last workgroup unit half empty
     (EDGES, 1024, 576),
+    # 34 output units: pieces of more than 64 rows (the units of smaller ones
+    # would be (24 + 44) * 9 > the workgroups), the last unit half empty
+    (EDGES, 1088, 576),
+    # 180 and 90 units, pieces of more than 64 rows in both projections
+    ((200, 70, 40, 20, 17, 5, 4, 3, 2, 2, 1, 1, 1, 1, 1, 1), 2880, 2880),
     ((3,), 128, 64),       # fewer units than workgroups
     ((1,) * 63 + (200,), 192, 640),
-], ids=["64x64", "320x192", "1024x576", "one-group", "one-hot"])
+], ids=["64x64", "320x192", "1024x576", "1088x576", "2880x2880", "one-group", "one-hot"])
 def test_stream_forward(dev, loads, D, F):
     import torch
     cfg = _cfg(loads, D, F)
     run = LayerRun(cfg, 1, dev)
     L = run.layer
     L.out_perm.fill_(float("nan"))
+    mark_workspace(L)
     run.forward(-1)
+    assert not ran_tiles(L)
     n = cfg.T
     out = L.out_perm[:n].clone()
     groups = L.bufs.groups[:L.bufs.info_dict()["n_groups"]].cpu().tolist()
@@ -69,8 +77,10 @@ def test_stream_forward(dev, loads, D, F):
     b.plan(big.ids)
     b.permute(big.ids, big.gates, big.x)
     b.x_perm[:n] = L.x_perm[:n]  # experts keep their rows' places
+    mark_workspace(b)
     b.ffn(big.gu, big.dn, -1, save_gate_up=True)
     torch.cuda.synchronize()
+    assert ran_tiles(b)
     assert torch.equal(b.out_perm[:n], out)
     assert torch.equal(b.gate_up[:n], gu)
 
@@ -102,6 +112,56 @@ def test_stream_one_device_and_plans(dev, loads, P):
         at += rows[d]
     L.set_mode("ep")
     assert torch.equal(run.forward(-1), y)
+
+
+@pytest.mark.parametrize("loads", [
+    # most experts with a few rows, some of every class, two spread over devices
+    tuple(0 if e % 7 == 3 else 1 + e % 5 + 30 * (e % 61 == 8) + 1300 * (e == 77) + 330 * (e == 509)
+          for e in range(512)),
+    tuple(8 for _ in range(512)),
+], ids=["spread", "even"])
+def test_stream_most_experts_and_devices(dev, loads):
+    """512 experts on 64 devices: the same bits as the tiles, which run when
+    another 4200 pairs of the last expert follow."""
+    import torch
+    from paper_2601_17111_amd import binding as B
+    from paper_2601_17111_amd.layer import LLEPLayer
+    D, F, P, n = 192, 256, 64, sum(loads)
+    cfg = _cfg(loads, D, F, P=P).with_(alpha=Fraction(1))
+    assert n <= 4096
+    run = LayerRun(cfg, 4, dev)
+    L = run.layer
+    mark_workspace(L)
+    run.forward(-1)
+    assert not ran_tiles(L)
+    rows = L.pair_row.reshape(-1).long()
+    out = L.out_perm[rows]
+    T = n + 4200
+    ids = torch.full((T, 1), 511, dtype=torch.int32, device=dev)
+    ids[:n] = run.ids
+    x = torch.zeros((T, D), dtype=torch.bfloat16, device=dev)
+    x[:n] = run.x
+    big = LLEPLayer(T, 1, cfg.E, P, D, F, T // P + 1, torch.bfloat16, dev)
+    mark_workspace(big)
+    big.forward(ids, torch.ones((T, 1), device=dev), x, run.gu, run.dn)
+    torch.cuda.synchronize()
+    assert ran_tiles(big)
+    assert not big.bufs.info_dict()["status"] & B.LLEP_STATUS_FFN_WAIT
+    assert torch.equal(big.out_perm[big.pair_row[:n].reshape(-1).long()], out)
+    # one device at a time, and a sample against the oracle
+    full = L.out_perm.clone()
+    L.out_perm.fill_(float("nan"))
+    for d in range(P):
+        L.ffn(run.gu, run.dn, d)
+    torch.cuda.synchronize()
+    assert torch.equal(L.out_perm, full)
+    sample = np.linspace(0, n - 1, 40).astype(int)
+    W = run.host_weights(set(run.inp.ids[sample, 0].tolist()))
+    got = out.float().cpu().numpy()
+    for p in sample:
+        w = (m.astype(np.float64) for m in W[int(run.inp.ids[p, 0])])
+        want = oracle.swiglu_ffn(run.inp.x[p:p + 1].astype(np.float64), *w)[0]
+        assert rel_err(got[p], want) <= TOL_BF16, p
 
 
 @pytest.mark.parametrize("T,E,P,D,F,tiles", [
