@@ -253,9 +253,9 @@ __device__ __forceinline__ void stream_units(const StreamArgs &a, const StreamTa
   constexpr int kStage = kPer * kShare * 1024;
   constexpr int kRingBytes = kStreamLds / kStreamWaves * kShare;
   constexpr int kRing = kRingBytes / kStage;  // stages
-  static_assert(kD * kA % kShare == 0 && kRing >= 3 && (kRing - 1) * kPer < 64 && kD <= 2, "ring");
+  static_assert(kD * kA % kShare == 0 && kRing >= 3 && (kRing - 1) * kPer < 64, "ring");
   // two slices of a row-major A are 128 contiguous bytes per row: whole lines
-  constexpr bool kWide = kPhase == 0 && kD == 2;
+  static_assert(kPhase != 0 || kD == 2, "the layout of x_perm's rows below");
   if (count <= 0) return;
   const int32_t *list = t.list + class_at;
   const uint16_t *first = t.first + class_at;
@@ -318,12 +318,10 @@ __device__ __forceinline__ void stream_units(const StreamArgs &a, const StreamTa
 #pragma unroll
     for (int j = 0; j < kAPer; ++j) {
       const int ja = wave * kAPer + j;  // KB of the stage's A
-      if (kWide) {  // 8 rows of 128 bytes; chunk swizzled by (row / 2) % 8
+      if (kPhase == 0) {  // 8 rows of 128 bytes; chunk swizzled by (row / 2) % 8
         const int r = 8 * ja + (lane >> 3);
         offA[j] = row_off(r) + (((lane & 7) ^ ((r >> 1) & 7)) << 4);
-      } else if (kPhase == 0) {  // slice ja / kA, 16 rows of 64 bytes
-        offA[j] = row_off(16 * (ja % kA) + (lane >> 2)) + kc_load * 16 + ja / kA * 64;
-      } else {
+      } else {  // slice ja / kA, a block of 16 rows x 64 bytes
         offA[j] = min(ja % kA, (q.rows - 1) >> 4) * stride + blk_lane + ja / kA * 1024;
       }
     }
@@ -331,7 +329,7 @@ __device__ __forceinline__ void stream_units(const StreamArgs &a, const StreamTa
   setup();
   int q_k = 0, issued = 0;
   uint32_t q_stage = ring0;
-  // a stage in LDS: A (kWide: rows of 128 bytes; else per slice kA blocks of
+  // a stage in LDS: A (gate/up: rows of 128 bytes; down: per slice kA blocks of
   // 16 rows x 64 bytes), then per wave and slice kB blocks of the weights
   auto request = [&]() {
     // The weights first: they come from memory, the rows mostly from the L2.
@@ -404,8 +402,8 @@ __device__ __forceinline__ void stream_units(const StreamArgs &a, const StreamTa
         for (int m = 0; m < kMT; ++m) {
           const int r = kA == 1 ? lane & 15 : row_w + m * 32 + (lane & 31);
           fa[s][m] = *reinterpret_cast<const bf16x8 *>(
-              kWide ? &a_s[r * 64 + (((2 * s + h) ^ ((r >> 1) & 7)) << 3)]
-                    : &a_s[(s >> 1) * kA * 512 + lds_swz32(r, kc)]);
+              kPhase == 0 ? &a_s[r * 64 + (((2 * s + h) ^ ((r >> 1) & 7)) << 3)]
+                          : &a_s[(s >> 1) * kA * 512 + lds_swz32(r, kc)]);
         }
       }
 #pragma unroll
