@@ -201,8 +201,9 @@ int llep_pack_weights(int32_t E, int32_t D, int32_t F, llep_dtype dtype,
  *   act = silu(X Wg_e) * (X Wu_e)   (float accumulation; rounded to dtype)
  *   out_perm[row_start : row_start + n] = act Wd_e   (float accumulation)
  * The group range is read from plan->group_begin on the device: no host
- * synchronization. Weights are the llep_pack_weights outputs. bf16 uses
- * matrix cores (MFMA); f32 is a plain reference-precision path.
+ * synchronization. Weights are the llep_pack_weights outputs. Both types run
+ * on matrix cores (MFMA); f32 has float32 operands, products and sums
+ * throughout (an element's sum over k in two interleaved chains).
  * Requires D % 64 == 0, F % 64 == 0 (both at most LLEP_MAX_FFN_DIM);
  * workspace of at least
  * llep_grouped_ffn_workspace_bytes(params, F, dtype) bytes, 256-byte aligned.
@@ -273,7 +274,7 @@ int llep_combine(const llep_plan_params *params, const void *out_perm,
                  const int32_t *pair_row, const float *topk_gates, int32_t D,
                  llep_dtype dtype, void *y, hipStream_t stream);
 
-/* ---- backward (bf16) ------------------------------------------------------
+/* ---- backward (bf16, f32) ---------------------------------------------------
  * The paper keeps LLEP exact under training: the gradients of the spilled
  * chunks computed on foreign devices go back to the expert's native device
  * and are added there (Sec. 1; Sec. 4). These calls give the backward of the
@@ -322,9 +323,9 @@ int llep_pack_weights_backward(int32_t E, int32_t D, int32_t F, llep_dtype dtype
  * totals each native device holds after the gradient return. Experts without
  * rows in the range are not written; rows outside the range are not
  * written. Weights are the llep_pack_weights (w_gate_up_packed) and
- * llep_pack_weights_backward outputs. bf16 uses matrix cores and rounds g,
- * u, dg, du and act to bf16 once each; f32 is a plain reference-precision
- * path (no intermediate rounding). g and u are read from gate_up when it
+ * llep_pack_weights_backward outputs. Both types run on matrix cores; bf16
+ * rounds g, u, dg, du and act to bf16 once each, f32 rounds nothing to fewer
+ * than 32 bits. g and u are read from gate_up when it
  * is non-null: the llep_grouped_ffn_train output for the same plan, x_perm
  * and weights, over the same device or over all devices (-1); the results
  * are then bit-identical to recomputing, and rows that call did not write
@@ -332,9 +333,8 @@ int llep_pack_weights_backward(int32_t E, int32_t D, int32_t F, llep_dtype dtype
  * grouped GEMM, into the workspace). Workspace of at least
  * llep_grouped_ffn_backward_workspace_bytes bytes, 256-byte aligned.
  * Requires D % 64 == 0, F % 64 == 0 (at most LLEP_MAX_FFN_DIM); dw_*
- * 16-byte aligned; T*K below about
- * 4.19 M pairs (the weight-gradient operands, each expert's rows end to end,
- * are addressed with 32-bit byte offsets; LLEP_E_ARG beyond).
+ * 16-byte aligned; T*K + 32 (2E + P), rounded up to a multiple of 32, below
+ * 2^22 (LLEP_E_ARG beyond; a limit of this call, for both types).
  * Errors: LLEP_E_ARG, LLEP_E_DTYPE, LLEP_E_WORKSPACE. */
 size_t llep_grouped_ffn_backward_workspace_bytes(const llep_plan_params *params,
                                                  int32_t D, int32_t F,

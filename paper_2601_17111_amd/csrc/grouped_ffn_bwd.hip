@@ -57,10 +57,11 @@ static size_t f32_bwd_bytes(int64_t R, int32_t F) {
 }
 
 bool ffn_backward_rows_ok(int64_t R, int32_t E, int32_t P) {
-  // the documented limit of the call: 512 bytes for each of the rows, the
-  // groups padded to 32, in 31 bits
+  // A limit of the interface: the rows, with every group that a plan can have
+  // padded to 32, are fewer than 2^22. (No operand needs it: wgrad.h takes a
+  // group from a 64-bit base, and what it accepts is not changed.)
   const int64_t max_groups = 2 * int64_t(E) + P;
-  return (R + 32 * max_groups + 31) / 32 * 32 * 512 <= int64_t(INT32_MAX);
+  return (R + 32 * max_groups + 31) / 32 * 32 < (int64_t(1) << 22);
 }
 
 size_t ffn_backward_workspace_bytes(int64_t R, int32_t E, int32_t P, int32_t D, int32_t F,

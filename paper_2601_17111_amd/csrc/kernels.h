@@ -79,8 +79,8 @@ struct FfnArgs {
 size_t ffn_workspace_bytes(int64_t R, int32_t E, int32_t P, int32_t F,
                            llep_dtype dtype);
 hipError_t launch_grouped_ffn(const FfnArgs &a, hipStream_t stream);
-// The bf16 forward of calls of few rows (stream_ffn.hip): R pairs over all
-// devices, at most kStreamRows; act: the workspace's activation.
+// The bf16 forward of calls of few rows (stream_ffn.hip), at most kStreamRows
+// over all devices; act: the workspace's activation.
 constexpr int kStreamRows = 4096;
 bool use_stream_ffn(const FfnArgs &a);
 hipError_t launch_stream_ffn(const FfnArgs &a, void *act, hipStream_t stream);
@@ -107,11 +107,10 @@ struct FfnBwdArgs {
 };
 size_t ffn_backward_workspace_bytes(int64_t R, int32_t E, int32_t P, int32_t D, int32_t F,
                                     llep_dtype dtype);
-// false when the weight-gradient operands of R rows are too long for the
-// GEMM's 32-bit per-lane byte offsets
+// whether R rows are within the call's documented limit
 bool ffn_backward_rows_ok(int64_t R, int32_t E, int32_t P);
 hipError_t launch_grouped_ffn_backward(const FfnBwdArgs &a, hipStream_t stream);
-// zeros for the weight gradients of the experts without a group in the range
+// zeros for the weight gradients of the experts without rows in the range
 hipError_t launch_zero_absent(const FfnBwdArgs &a, hipStream_t stream);
 hipError_t launch_pack_backward(int32_t E, int32_t D, int32_t F, llep_dtype dtype, const void *w_gate,
                                 const void *w_up, const void *w_down, void *gut, void *dnt,

@@ -4,8 +4,11 @@
 //
 // Both are bound by HBM (every element read once and written once). A
 // wavefront takes a unit of 8 KB, 64 columns of kRows consecutive rows: eight
-// 16-byte loads per lane are in flight before the first is used, every load
-// covers whole 128-byte lines and every store one contiguous 1 KB run.
+// 16-byte loads per lane are in flight before the first is used, and every
+// store is one contiguous 1 KB run. The forward's loads cover whole 128-byte
+// lines. The backward's cover the 32 columns of a block, in bf16 half a line
+// whose other half is the unit's next load; from sources that do not start on
+// 16-byte boundaries it reads element by element.
 // gpt-oss-20b layer (32 experts, D = F = 2880, bf16; 3.19 GB moved by each
 // call): forward 1260 -> 592 us, backward 1149 -> 584 us (5.4 TB/s) against
 // kernels that moved 2 bytes per lane and instruction.

@@ -2,7 +2,9 @@
 //
 // hist_kernel   counts, per rank tile of kRankTile pairs and per slice of
 //               kRankSub pairs, how many pairs go to each expert (Alg. 4,
-//               first step: the global per-expert loads).
+//               first step: the global per-expert loads). Calls of at most
+//               kPlanHistPairs pairs have no such launch: the plan kernel
+//               counts them.
 // plan_kernel   one workgroup: scans the tile counts into per-tile rank bases
 //               and the loads l, runs the lambda test (Alg. 4), then the
 //               least-loaded assignment (Alg. 2 with the spill loop of

@@ -215,7 +215,7 @@ def test_backward_argument_checks():
     assert zero(0, 64, 96, a) == B.LLEP_E_ARG
     assert zero(0, 64, 128, None) == B.LLEP_E_ARG
     assert zero(0, 64, 128, ctypes.c_void_p(4100)) == B.LLEP_E_ARG
-    # more pairs than the backward's 32-bit operand offsets reach
+    # more pairs than the call's limit of about 2^22
     big = B.make_params(1 << 20, 8, 8, 4, (1 << 23) // 4)
     nb = B.llep_grouped_ffn_backward_workspace_bytes(big, 64, 128, bf)
     assert L.llep_grouped_ffn_backward(ctypes.byref(big), ctypes.byref(bufs), 0, a, a, a, a, a,
